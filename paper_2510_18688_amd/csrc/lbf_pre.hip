@@ -1,12 +1,10 @@
 // Cahn-Hilliard smoothing of a binary solid image (contract in
-// include/lbf_pre.h).  One fused pass per Euler step: a workgroup loads its
-// tile of c with a two-node halo into LDS, computes the chemical potential
-// on the tile plus a one-node ring, and updates c on the tile, so HBM sees
-// one read and one write of c per node and step (the halo re-reads hit L2:
-// tiles are dealt to the XCDs in contiguous bands).  Each lane owns columns
-// of the boxes and slides a window of registers along them.
+// include/lbf_pre.h).  Wavefronts march along the image with the windows of the
+// stencils in registers: four Euler steps a pass in 2D, one in 3D.  The first
+// pass reads the image itself and the last one writes phi0.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -30,254 +28,296 @@ namespace {
 
 constexpr long long kMaxNodesCH = 0x7FFFFFFFLL;
 
-// tiles: 64 x 16 nodes in 2D, 32 x 8 x 4 in 3D (1024 nodes, 4 per lane)
-constexpr int kTX2 = 64, kTY2 = 16;
-constexpr int kTX3 = 32, kTY3 = 8, kTZ3 = 4;
+// 2D pass: Euler steps, columns per lane, rows in flight per lane, wavefronts
+// wanted; 3D pass: rows per lane, wavefronts wanted.
+//
+// Both passes are bound by vector instructions once enough wavefronts are in
+// flight, and the strips' overlaps are recomputed: longer strips waste less and
+// leave fewer wavefronts to hide the latencies.  Microseconds per Euler step,
+// 4096 x 2048: 4 steps a pass, 1 column a lane, 2048 / 3072 / 4096 / 5500
+// wavefronts 13.4 / 10.5 / 10.2 / 10.9; 3 steps 14.1 / 10.7 / 11.3 / 10.3; 2 steps
+// 15.3 / 12.2 / 11.1 / 11.0; 1 step (4096) 16.3; 6 steps 14.8 / 11.4 / 13.2 / 12.2; 2
+// columns a lane, 4 steps 11.6 / 12.2 / 12.5 / 13.4; 8 rows in flight instead of 4
+// within 2 %.  256^3: 4 rows a lane, 2280 / 3040 / 4180 / 6080 wavefronts 58.5 / 41.7
+// / 46.1 / 40.5; 6 rows 51.6 / 45.5 / 45.8 / 44.3; 8 rows 55.2 / 52.5 / 45.1 / 47.1; every
+// wavefront with its own overlap along y (no LDS) 45 at best.  One step a pass
+// through a tile of c and of mu in LDS took 25.2 (2D) and 98 (3D).
+constexpr int kT2 = 4, kV2 = 1, kPF2 = 4, kWaves2 = 4096;
+constexpr int kR3 = 4, kWaves3 = 6144;
 
 struct ChGeo {
   int n[3];
   int per[3];
 };
 
-// Index of v along an axis of n nodes: wrapped (any offset), or clamped to
-// the first and last node (the mirror ghost).
-__device__ __forceinline__ int wrap_or_clamp(int v, int n, int periodic) {
-  if (v >= 0 && v < n) return v;   // interior: no division
-  if (periodic) {
-    v %= n;
-    return v < 0 ? v + n : v;
+// Source node of index v along an axis of n nodes: wrapped, or reflected at
+// the walls (-1 -> 0, -2 -> 1, n -> n - 1, ...).  The model's ghost repeats the
+// first node beyond a wall at every step, and the stencil below treats both
+// directions of an axis alike to the last bit, so the reflected continuation
+// of the data stays the reflected continuation of the result and the ghost of
+// c and of mu needs no step of its own.
+__device__ __forceinline__ int source_node(int v, int n, int periodic) {
+  while (v < 0 || v >= n) {   // once at most, unless the image is narrower than a strip's overlap
+    if (v < 0) v = periodic ? v + n : -1 - v;
+    else v = periodic ? v - n : n - 1 - (v - n);
   }
-  return v < 0 ? 0 : n - 1;
+  return v;
 }
 
-// 6 sum_i w_i (X(x + c_i) - X(x)) over an LDS box with row length SX and
-// plane size SXY: D2Q9 (DIM 2) or D3Q19 (DIM 3) weights.
-template <int DIM, int SX, int SXY>
-__device__ __forceinline__ float lds_laplacian(const float* X, int i) {
-  const float xc = X[i];
-  float axis = 0.0f, diag = 0.0f;
-  constexpr int zlo = DIM == 3 ? -1 : 0, zhi = DIM == 3 ? 1 : 0;
-#pragma unroll
-  for (int dz = zlo; dz <= zhi; ++dz)
-#pragma unroll
-    for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int m = (dx != 0) + (dy != 0) + (dz != 0);
-        if (m == 0 || m == 3) continue;
-        const float v = X[i + dz * SXY + dy * SX + dx] - xc;
-        if (m == 1) axis += v;
-        else diag += v;
-      }
-  // D2Q9: 1/9 axes, 1/36 diagonals; D3Q19: 1/18 axes, 1/36 face diagonals
-  constexpr float wa = DIM == 3 ? 1.0f / 18.0f : 1.0f / 9.0f;
-  return 6.0f * (wa * axis + (1.0f / 36.0f) * diag);
+// The wavefront's place in its workgroup, as a scalar: what a strip derives
+// from it (rows, bounds, addresses) then costs no vector instruction.
+__device__ __forceinline__ int wave_of_block() {
+  return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 }
 
-// The 2D step with the work laid out by columns: lane (tx, ty) of a 64 x 4
-// block owns column tx of the tile and a run of consecutive rows, and slides
-// a 3 x 3 window of registers up its column, so each stencil reads three new
-// LDS values instead of nine and the box indices are formed once per column.
-// Same operands, in the same order, as lds_laplacian<2, ...>.
-template <int TX, int TY>
+// The value of the next or previous lane of the wavefront (zero beyond its ends).
+__device__ __forceinline__ float next_lane(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float prev_lane(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
+}
+
+// Both lattices' Laplacians 6 sum_i w_i (X(x + c_i) - X(x)) are sums of second
+// differences d_x, d_y, d_z (d_x X = (X(x + 1) - X) - (X - X(x - 1))) and their
+// products: D2Q9 d_x + d_y + d_x d_y / 6, D3Q19 d_x + d_y + d_z + (d_x d_y +
+// d_y d_z + d_x d_z) / 6.  Marching along an axis, a second difference costs two
+// subtractions (the first difference is carried), so a Laplacian takes 8 (2D) or
+// 13 (3D) operations instead of 19 or 37, every one on differences of
+// neighbours: nothing of order X is added up.
+//
+// No contraction but the written ones: each step rounds alike however many
+// steps a launch makes.
+
+__device__ __forceinline__ float ch_mu(float c, float lap, float A, float kappa) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(A, __builtin_fmaf(c * c, c, -c), -(kappa * lap));
+}
+
+__device__ __forceinline__ float ch_out(float c, bool final) {
+  return final ? fminf(fmaxf(0.5f * (1.0f + c), 0.0f), 1.0f) : c;
+}
+
+// Element x of the row at `row`: of the image at its first step (img set), else
+// of the plane of c.
+__device__ __forceinline__ float ch_in(const float* __restrict__ c, const uint8_t* __restrict__ img,
+                                       long long row, int x) {
+  if (img) return (img + row)[x] ? 1.0f : -1.0f;
+  return (c + row)[x];
+}
+
+// ---- 2D: T Euler steps in one pass.  A wavefront owns 64 V adjacent columns
+// (V per lane) and marches up the rows with every step's window in registers,
+// step t two rows behind step t - 1: neighbours along x come from the lane
+// next door, along y from the carried differences.  Nothing passes through
+// LDS and no wavefront waits for another.  Each step uses up two columns on
+// either side and two rows at either end, which a strip recomputes.
+
+// Window of one step: the value at the last row seen (c, mu), its d_x (a) and
+// the first differences along y of both; c of the row before.
+template <int V>
+struct ChWin2 {
+  float c[V], c1[V], ec[V], a[V], ea[V], mu[V], em[V], am[V], eam[V];
+};
+
+template <int V>
+__device__ __forceinline__ void second_diff_x(const float* c, float* a) {
+#pragma clang fp contract(off)
+  float e[V];
+#pragma unroll
+  for (int v = 0; v + 1 < V; ++v) e[v] = c[v + 1] - c[v];
+  e[V - 1] = next_lane(c[0]) - c[V - 1];
+  a[0] = e[0] - prev_lane(e[V - 1]);
+#pragma unroll
+  for (int v = 1; v < V; ++v) a[v] = e[v] - e[v - 1];
+}
+
+// A row of a step's input enters its window (row); the step's result two rows
+// before it takes its place.
+template <int V>
+__device__ __forceinline__ void ch_advance2(ChWin2<V>& w, float* row, float A, float kappa,
+                                            float dtM) {
+#pragma clang fp contract(off)
+  constexpr float sixth = 1.0f / 6.0f;
+  float a[V], mu[V], am[V];
+  second_diff_x<V>(row, a);
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const float ec = row[v] - w.c[v], ea = a[v] - w.a[v];
+    const float lap = __builtin_fmaf(sixth, ea - w.ea[v], w.a[v] + (ec - w.ec[v]));
+    mu[v] = ch_mu(w.c[v], lap, A, kappa);
+    w.ec[v] = ec;
+    w.ea[v] = ea;
+    w.a[v] = a[v];
+  }
+  second_diff_x<V>(mu, am);
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const float em = mu[v] - w.mu[v], eam = am[v] - w.am[v];
+    const float lap = __builtin_fmaf(sixth, eam - w.eam[v], w.am[v] + (em - w.em[v]));
+    const float next = __builtin_fmaf(dtM, lap, w.c1[v]);
+    w.em[v] = em;
+    w.eam[v] = eam;
+    w.mu[v] = mu[v];
+    w.am[v] = am[v];
+    w.c1[v] = w.c[v];
+    w.c[v] = row[v];
+    row[v] = next;
+  }
+}
+
+template <int T, int V, int PF>
 __global__ __launch_bounds__(256) void k_ch_step2(ChGeo G, const float* __restrict__ c,
+                                                  const uint8_t* __restrict__ img,
                                                   float* __restrict__ cn, float A, float kappa,
-                                                  float dtM, int ntx, int ntiles) {
-  static_assert(TX == 64 && TY % 4 == 0, "64 lanes per row, four row groups");
-  constexpr int LX = TX + 4, LY = TY + 4;   // c box, halo 2
-  constexpr int MX = TX + 2, MY = TY + 2;   // mu box, halo 1
-  constexpr float wa = 1.0f / 9.0f, wd = 1.0f / 36.0f;
-  __shared__ float cs[LX * LY];
-  __shared__ float ms[MX * MY];
-  const int t = lbf::xcd_tile(blockIdx.x, ntiles);
-  const int x0 = (t % ntx) * TX, y0 = (t / ntx) * TY;
+                                                  float dtM, int rows, int nsx, int nstrips,
+                                                  int final) {
+  constexpr int W = 64 * V - 4 * T;   // columns a strip delivers
+  const int t = lbf::xcd_tile(blockIdx.x, gridDim.x) * 4 + wave_of_block();
+  if (t >= nstrips) return;
   const int nx = G.n[0], ny = G.n[1];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  {
-    const int gx = wrap_or_clamp(x0 + tx - 2, nx, G.per[0]);
-    for (int ly = ty; ly < LY; ly += 4) {
-      const int gy = wrap_or_clamp(y0 + ly - 2, ny, G.per[1]);
-      cs[ly * LX + tx] = c[gy * nx + gx];
-    }
-    const int e = threadIdx.x;   // the last four columns of the box
-    if (e < 4 * LY) {
-      const int lx = TX + (e & 3), ly = e >> 2;
-      const int gx2 = wrap_or_clamp(x0 + lx - 2, nx, G.per[0]);
-      const int gy2 = wrap_or_clamp(y0 + ly - 2, ny, G.per[1]);
-      cs[ly * LX + lx] = c[gy2 * nx + gx2];
-    }
-  }
-  __syncthreads();
-  {
-    // mu on rows [r0, r1) of column tx; the window holds c rows my .. my + 2
-    // of box columns tx .. tx + 2 (centre (my + 1, tx + 1))
-    constexpr int RG = (MY + 3) / 4;
-    const int r0 = ty * RG, r1 = min(r0 + RG, MY);
-    float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, b0 = 0.0f, b1 = 0.0f, b2 = 0.0f;
-    if (r0 < r1) {
-      a0 = cs[r0 * LX + tx]; a1 = cs[r0 * LX + tx + 1]; a2 = cs[r0 * LX + tx + 2];
-      b0 = cs[(r0 + 1) * LX + tx]; b1 = cs[(r0 + 1) * LX + tx + 1]; b2 = cs[(r0 + 1) * LX + tx + 2];
-    }
-    for (int my = r0; my < r1; ++my) {
-      const float c0 = cs[(my + 2) * LX + tx], c1 = cs[(my + 2) * LX + tx + 1],
-                  c2 = cs[(my + 2) * LX + tx + 2];
-      const float xc = b1;
-      float axis = 0.0f, diag = 0.0f;
-      diag += a0 - xc; axis += a1 - xc; diag += a2 - xc;
-      axis += b0 - xc; axis += b2 - xc;
-      diag += c0 - xc; axis += c1 - xc; diag += c2 - xc;
-      const float lap = 6.0f * (wa * axis + wd * diag);
-      ms[my * MX + tx] = A * (xc * xc * xc - xc) - kappa * lap;
-      a0 = b0; a1 = b1; a2 = b2;
-      b0 = c0; b1 = c1; b2 = c2;
-    }
-    const int e = threadIdx.x;   // the last two columns of the mu box
-    if (e < 2 * MY) {
-      const int mx = TX + (e & 1), my = e >> 1;
-      const int j = (my + 1) * LX + mx + 1;
-      const float cc = cs[j];
-      ms[my * MX + mx] = A * (cc * cc * cc - cc) - kappa * lds_laplacian<2, LX, LX * LY>(cs, j);
-    }
-  }
-  __syncthreads();
-  if ((!G.per[0] && (x0 == 0 || x0 + TX >= nx)) || (!G.per[1] && (y0 == 0 || y0 + TY >= ny))) {
-    // beyond a mirror wall the potential is that of the first node
-    for (int i = threadIdx.x; i < MX * MY; i += 256) {
-      const int mx = i % MX, my = i / MX;
-      const int gx = x0 + mx - 1, gy = y0 + my - 1;
-      const int sx = G.per[0] ? gx : min(max(gx, 0), nx - 1);
-      const int sy = G.per[1] ? gy : min(max(gy, 0), ny - 1);
-      if (sx != gx || sy != gy) ms[i] = ms[(sy - y0 + 1) * MX + sx - x0 + 1];
-    }
-    __syncthreads();
-  }
-  {
-    // update on rows [o0, o0 + TY / 4) of column tx; window over mu rows
-    constexpr int RO = TY / 4;
-    const int o0 = ty * RO, gx = x0 + tx;
-    float a0 = ms[o0 * MX + tx], a1 = ms[o0 * MX + tx + 1], a2 = ms[o0 * MX + tx + 2];
-    float b0 = ms[(o0 + 1) * MX + tx], b1 = ms[(o0 + 1) * MX + tx + 1],
-          b2 = ms[(o0 + 1) * MX + tx + 2];
-    for (int oy = o0; oy < o0 + RO; ++oy) {
-      const float c0 = ms[(oy + 2) * MX + tx], c1 = ms[(oy + 2) * MX + tx + 1],
-                  c2 = ms[(oy + 2) * MX + tx + 2];
-      const float xc = b1;
-      float axis = 0.0f, diag = 0.0f;
-      diag += a0 - xc; axis += a1 - xc; diag += a2 - xc;
-      axis += b0 - xc; axis += b2 - xc;
-      diag += c0 - xc; axis += c1 - xc; diag += c2 - xc;
-      const float lap = 6.0f * (wa * axis + wd * diag);
-      const int gy = y0 + oy;
-      if (gx < nx && gy < ny) cn[gy * nx + gx] = cs[(oy + 2) * LX + tx + 2] + dtM * lap;
-      a0 = b0; a1 = b1; a2 = b2;
-      b0 = c0; b1 = c1; b2 = c2;
-    }
-  }
-}
-
-// Laplacian of the centre of three 3 x 3 slices (z - 1, z, z + 1; entry
-// 3 (dy + 1) + dx + 1) with the D3Q19 weights, accumulated in the order of
-// lds_laplacian<3, ...>.
-__device__ __forceinline__ float slice_laplacian19(const float* p, const float* q,
-                                                   const float* r) {
-  const float xc = q[4];
-  float axis = 0.0f, diag = 0.0f;
-  diag += p[1] - xc; diag += p[3] - xc; axis += p[4] - xc; diag += p[5] - xc; diag += p[7] - xc;
-  diag += q[0] - xc; axis += q[1] - xc; diag += q[2] - xc;
-  axis += q[3] - xc; axis += q[5] - xc;
-  diag += q[6] - xc; axis += q[7] - xc; diag += q[8] - xc;
-  diag += r[1] - xc; diag += r[3] - xc; axis += r[4] - xc; diag += r[5] - xc; diag += r[7] - xc;
-  return 6.0f * ((1.0f / 18.0f) * axis + (1.0f / 36.0f) * diag);
-}
-
-// the 3 x 3 neighbourhood of (x, y) in slice z of an LDS box
-template <int SX, int SXY>
-__device__ __forceinline__ void load_slice(const float* X, int x, int y, int z, float* out) {
+  const int xs = (t % nsx) * W, ys = (t / nsx) * rows, ye = min(ys + rows, ny);
+  const int lane = threadIdx.x & 63;
+  int gx[V], ox[V];
 #pragma unroll
-  for (int dy = -1; dy <= 1; ++dy)
+  for (int v = 0; v < V; ++v) {
+    const int col = lane * V + v - 2 * T;   // column of the strip
+    gx[v] = source_node(xs + col, nx, G.per[0]);
+    ox[v] = col >= 0 && col < W && xs + col < nx ? xs + col : -1;
+  }
+  const int r0 = ys - 2 * T, r1 = ye + 2 * T;
+  auto load = [&](int r, float* b) {
+    const long long row = (long long)source_node(r, ny, G.per[1]) * nx;
 #pragma unroll
-    for (int dx = -1; dx <= 1; ++dx) out[(dy + 1) * 3 + dx + 1] = X[z * SXY + (y + dy) * SX + x + dx];
+    for (int v = 0; v < V; ++v) b[v] = ch_in(c, img, row, gx[v]);
+  };
+  float buf[PF][V];
+#pragma unroll
+  for (int k = 0; k < PF; ++k) load(r0 + k, buf[k]);
+  ChWin2<V> w[T] = {};
+  for (int r = r0; r < r1; r += PF) {
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {
+      float q[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) q[v] = buf[k][v];
+      load(r + k + PF, buf[k]);
+#pragma unroll
+      for (int s = 0; s < T; ++s) ch_advance2<V>(w[s], q, A, kappa, dtM);
+      const int ro = r + k - 2 * T;
+      if (ro >= ys && ro < ye) {
+        float* o = cn + (long long)ro * nx;
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+          if (ox[v] >= 0) o[ox[v]] = ch_out(q[v], final != 0);
+      }
+    }
+  }
 }
 
-// The 3D step with the work laid out by columns along z: a lane owns an
-// (x, y) column of a box and slides three slices of its 3 x 3 neighbourhood
-// up the column, so each stencil reads nine new LDS values instead of
-// eighteen and the box indices are formed once per column.
-template <int TX, int TY, int TZ>
-__global__ __launch_bounds__(256) void k_ch_step3(ChGeo G, const float* __restrict__ c,
-                                                  float* __restrict__ cn, float A, float kappa,
-                                                  float dtM, int ntx, int nty, int ntiles) {
-  static_assert(TX * TY == 256, "one output column per lane");
-  constexpr int LX = TX + 4, LY = TY + 4, LZ = TZ + 4;   // c box, halo 2
-  constexpr int MX = TX + 2, MY = TY + 2, MZ = TZ + 2;   // mu box, halo 1
-  __shared__ float cs[LX * LY * LZ];
-  __shared__ float ms[MX * MY * MZ];
-  const int t = lbf::xcd_tile(blockIdx.x, ntiles);
-  const int x0 = (t % ntx) * TX, y0 = ((t / ntx) % nty) * TY, z0 = (t / (ntx * nty)) * TZ;
+// ---- 3D: one Euler step per pass, marching along z.  A workgroup's four
+// wavefronts own 60 columns and 4 R - 2 rows, R rows of one column per lane;
+// neighbours along x come from the lanes next door, along y from the lane's own
+// rows, along z from the carried differences.  c is loaded with one row more on
+// either side; only mu of a wavefront's outer rows passes through LDS, to the
+// wavefronts above and below (one barrier per slab, two buffers), so the rows
+// between wavefronts are not computed twice.
+template <int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_ch_step3(
+    ChGeo G, const float* __restrict__ c, const uint8_t* __restrict__ img, float* __restrict__ cn,
+    float A, float kappa, float dtM, int slabs, int nsx, int nsy, int final) {
+#pragma clang fp contract(off)
+  constexpr int W = 60, H = 4 * R - 2;
+  constexpr float sixth = 1.0f / 6.0f;
+  __shared__ float edge[2][4][2][64];   // [slab parity][wavefront][first, last row][lane]
+  const int t = lbf::xcd_tile(blockIdx.x, gridDim.x);
   const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
-  for (int col = threadIdx.x; col < LX * LY; col += 256) {
-    const int lx = col % LX, ly = col / LX;
-    const int gx = wrap_or_clamp(x0 + lx - 2, nx, G.per[0]);
-    const int gy = wrap_or_clamp(y0 + ly - 2, ny, G.per[1]);
+  const int wv = wave_of_block(), lane = threadIdx.x & 63;
+  const int xs = (t % nsx) * W, yb = ((t / nsx) % nsy) * H, zs = (t / (nsx * nsy)) * slabs;
+  const int ys = yb - 1 + wv * R;   // the lane's first row
+  const int ze = min(zs + slabs, nz);
+  const int gx = source_node(xs + lane - 2, nx, G.per[0]);
+  const bool mine = lane >= 2 && lane < 62 && xs + lane - 2 < nx;
+  const int below = max(wv - 1, 0), above = min(wv + 1, 3);
+  int gy[R + 2];
 #pragma unroll
-    for (int lz = 0; lz < LZ; ++lz) {
-      const int gz = wrap_or_clamp(z0 + lz - 2, nz, G.per[2]);
-      cs[(lz * LY + ly) * LX + lx] = c[(gz * ny + gy) * nx + gx];   // < 2^31 nodes
-    }
-  }
-  __syncthreads();
-  for (int col = threadIdx.x; col < MX * MY; col += 256) {
-    const int mx = col % MX, my = col / MX;
-    float p[9], q[9], r[9];
-    load_slice<LX, LX * LY>(cs, mx + 1, my + 1, 0, p);
-    load_slice<LX, LX * LY>(cs, mx + 1, my + 1, 1, q);
+  for (int r = 0; r < R + 2; ++r) gy[r] = source_node(ys + r - 1, ny, G.per[1]) * nx;
+  const long long slab = (long long)nx * ny;
+  auto load = [&](int z, float* b) {
+    const long long base = source_node(z, nz, G.per[2]) * slab;
+    if (img) {
 #pragma unroll
-    for (int mz = 0; mz < MZ; ++mz) {
-      load_slice<LX, LX * LY>(cs, mx + 1, my + 1, mz + 2, r);
-      const float cc = q[4];
-      ms[(mz * MY + my) * MX + mx] = A * (cc * cc * cc - cc) - kappa * slice_laplacian19(p, q, r);
+      for (int r = 0; r < R + 2; ++r) b[r] = (img + base + gy[r])[gx] ? 1.0f : -1.0f;
+    } else {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        p[k] = q[k];
-        q[k] = r[k];
-      }
+      for (int r = 0; r < R + 2; ++r) b[r] = (c + base + gy[r])[gx];
     }
-  }
-  __syncthreads();
-  const bool at_wall = (!G.per[0] && (x0 == 0 || x0 + TX >= nx)) ||
-                       (!G.per[1] && (y0 == 0 || y0 + TY >= ny)) ||
-                       (!G.per[2] && (z0 == 0 || z0 + TZ >= nz));
-  if (at_wall) {
-    // beyond a mirror wall the potential is that of the first node
-    for (int i = threadIdx.x; i < MX * MY * MZ; i += 256) {
-      const int mx = i % MX, my = (i / MX) % MY, mz = i / (MX * MY);
-      const int gx = x0 + mx - 1, gy = y0 + my - 1, gz = z0 + mz - 1;
-      const int sx = G.per[0] ? gx : min(max(gx, 0), nx - 1);
-      const int sy = G.per[1] ? gy : min(max(gy, 0), ny - 1);
-      const int sz = G.per[2] ? gz : min(max(gz, 0), nz - 1);
-      if (sx != gx || sy != gy || sz != gz)
-        ms[i] = ms[((sz - z0 + 1) * MY + sy - y0 + 1) * MX + sx - x0 + 1];
+  };
+  // windows along z of c and of mu: the value at the last slab (and c of the
+  // one before), d_x + d_y (s), d_x d_y (q) and the first differences along z of
+  // the value and of s
+  float cz[R] = {}, c2[R] = {}, ez[R] = {}, s[R] = {}, es[R] = {}, q[R] = {};
+  float mz[R] = {}, em[R] = {}, sm[R] = {}, esm[R] = {}, qm[R] = {};
+  float nxt[R + 2];
+  load(zs - 2, nxt);
+  for (int z = zs - 2; z < ze + 2; ++z) {
+    float in[R + 2], a[R + 2], mu[R + 2];
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) in[r] = nxt[r];
+    if (z + 1 < ze + 2) load(z + 1, nxt);
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) {
+      const float e = next_lane(in[r]) - in[r];
+      a[r] = e - prev_lane(e);
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float sn = a[r + 1] + ((in[r + 2] - in[r + 1]) - (in[r + 1] - in[r]));
+      const float qn = (a[r + 2] - a[r + 1]) - (a[r + 1] - a[r]);
+      const float e = in[r + 1] - cz[r], f = sn - s[r];
+      const float lap = __builtin_fmaf(sixth, q[r] + (f - es[r]), s[r] + (e - ez[r]));
+      mu[r + 1] = ch_mu(cz[r], lap, A, kappa);
+      ez[r] = e;
+      es[r] = f;
+      s[r] = sn;
+      q[r] = qn;
+    }
+    float(*ed)[2][64] = edge[z & 1];
+    ed[wv][0][lane] = mu[1];
+    ed[wv][1][lane] = mu[R];
     __syncthreads();
-  }
-  {
-    const int ox = threadIdx.x % TX, oy = threadIdx.x / TX;
-    const int gx = x0 + ox, gy = y0 + oy;
-    float p[9], q[9], r[9];
-    load_slice<MX, MX * MY>(ms, ox + 1, oy + 1, 0, p);
-    load_slice<MX, MX * MY>(ms, ox + 1, oy + 1, 1, q);
+    mu[0] = ed[below][1][lane];
+    mu[R + 1] = ed[above][0][lane];
 #pragma unroll
-    for (int oz = 0; oz < TZ; ++oz) {
-      load_slice<MX, MX * MY>(ms, ox + 1, oy + 1, oz + 2, r);
-      const int gz = z0 + oz;
-      if (gx < nx && gy < ny && gz < nz)
-        cn[(gz * ny + gy) * nx + gx] = cs[((oz + 2) * LY + oy + 2) * LX + ox + 2] +
-                                       dtM * slice_laplacian19(p, q, r);
+    for (int r = 0; r < R + 2; ++r) {
+      const float e = next_lane(mu[r]) - mu[r];
+      a[r] = e - prev_lane(e);
+    }
+    const int zo = z - 2;
+    float* o = cn + zo * slab + xs + lane - 2;
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        p[k] = q[k];
-        q[k] = r[k];
-      }
+    for (int r = 0; r < R; ++r) {
+      const float sn = a[r + 1] + ((mu[r + 2] - mu[r + 1]) - (mu[r + 1] - mu[r]));
+      const float qn = (a[r + 2] - a[r + 1]) - (a[r + 1] - a[r]);
+      const float e = mu[r + 1] - mz[r], f = sn - sm[r];
+      const float lap = __builtin_fmaf(sixth, qm[r] + (f - esm[r]), sm[r] + (e - em[r]));
+      const float v = __builtin_fmaf(dtM, lap, c2[r]);
+      // (the workgroup's outer rows lack their neighbours' mu)
+      const int row = ys + r;
+      if (zo >= zs && row >= yb && row < yb + H && row < ny && mine)
+        o[(long long)row * nx] = ch_out(v, final != 0);
+      em[r] = e;
+      esm[r] = f;
+      sm[r] = sn;
+      qm[r] = qn;
+      mz[r] = mu[r + 1];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      c2[r] = cz[r];
+      cz[r] = in[r + 1];
     }
   }
 }
@@ -318,6 +358,38 @@ int ch_validate(const lbf_ch_params* p, int32_t iterations) {
   return LBF_OK;
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb && y < x + na;
+}
+
+// One pass of T steps over a 2D plane.
+template <int T>
+int ch_pass2(const ChGeo& G, const float* c, const uint8_t* img, float* cn, float A, float kappa,
+             float dtM, bool final, hipStream_t st) {
+  constexpr int W = 64 * kV2 - 4 * T;
+  const int nsx = ceil_div(G.n[0], W);
+  const long long want = ((long long)G.n[1] * nsx + kWaves2 - 1) / kWaves2;
+  const int rows = (int)std::max(8LL, (want + 3) / 4 * 4);
+  const int nstrips = nsx * ceil_div(G.n[1], rows);
+  hipLaunchKernelGGL((k_ch_step2<T, kV2, kPF2>), dim3(ceil_div(nstrips, 4)), dim3(256), 0, st, G, c, img,
+                     cn, A, kappa, dtM, rows, nsx, nstrips, final ? 1 : 0);
+  HIP_TRY(hipGetLastError());
+  return LBF_OK;
+}
+
+int ch_pass3(const ChGeo& G, const float* c, const uint8_t* img, float* cn, float A, float kappa,
+             float dtM, bool final, hipStream_t st) {
+  const int nsx = ceil_div(G.n[0], 60), nsy = ceil_div(G.n[1], 4 * kR3 - 2);
+  const long long cols = 4LL * nsx * nsy;   // wavefronts side by side
+  const int slabs = (int)std::max(4LL, ((long long)G.n[2] * cols + kWaves3 - 1) / kWaves3);
+  const int nblk = nsx * nsy * ceil_div(G.n[2], slabs);
+  hipLaunchKernelGGL((k_ch_step3<kR3>), dim3(nblk), dim3(256), 0, st, G, c, img, cn, A, kappa, dtM,
+                     slabs, nsx, nsy, final ? 1 : 0);
+  HIP_TRY(hipGetLastError());
+  return LBF_OK;
+}
+
 // The smoothing itself on two planes c0, c1 of at least plane_bytes(n) each
 // (c1 also stages a host image and, when phi0 is host memory, the result).
 // Stream-ordered; synchronises only when host memory is read or written.
@@ -325,37 +397,53 @@ int ch_run(const lbf_ch_params* p, const uint8_t* solid, bool solid_on_device, f
            bool phi0_on_device, int32_t iterations, hipStream_t st, float* c0, float* c1) {
   const int N = p->nx * p->ny * p->nz;
   float* c[2] = {c0, c1};
-  const int nb = (N + 255) / 256;
+  const int nb = (int)(((long long)N + 255) / 256);
   const ChGeo G{{p->nx, p->ny, p->nz},
                 {p->periodic[0] ? 1 : 0, p->periodic[1] ? 1 : 0, p->periodic[2] ? 1 : 0}};
   const bool is3d = p->nz > 1;
-  const int ntx = ceil_div(p->nx, is3d ? kTX3 : kTX2), nty = ceil_div(p->ny, is3d ? kTY3 : kTY2);
-  const int ntz = is3d ? ceil_div(p->nz, kTZ3) : 1;
-  const int ntiles = ntx * nty * ntz;
   const float A = (float)p->A, kap = (float)p->kappa, dtM = (float)(p->dt * p->mobility);
   const uint8_t* s = solid;
   if (!solid_on_device) {
     HIP_TRY(hipMemcpyAsync(c[1], solid, (size_t)N, hipMemcpyHostToDevice, st));
     s = (const uint8_t*)c[1];
   }
-  hipLaunchKernelGGL(k_ch_init, dim3(nb), dim3(256), 0, st, s, c[0], N);
-  HIP_TRY(hipGetLastError());
-  int cur = 0;
-  for (int it = 0; it < iterations; ++it) {
-    if (is3d)
-      hipLaunchKernelGGL((k_ch_step3<kTX3, kTY3, kTZ3>), dim3(ntiles), dim3(256), 0, st, G,
-                         c[cur], c[1 - cur], A, kap, dtM, ntx, nty, ntiles);
-    else
-      hipLaunchKernelGGL((k_ch_step2<kTX2, kTY2>), dim3(ntiles), dim3(256), 0, st, G, c[cur],
-                         c[1 - cur], A, kap, dtM, ntx, ntiles);
+  // The first pass reads the image and the last one writes phi0, unless the
+  // caller's buffers overlap each other or the planes (then c is copied in
+  // and out, as for no steps at all).
+  const size_t pb = (size_t)N * 4;
+  const bool apart = !overlap(s, (size_t)N, phi0, pb) && !overlap(s, (size_t)N, c0, pb) &&
+                     !overlap(phi0, pb, c0, pb) && !overlap(phi0, pb, c1, pb);
+  const bool fused = iterations > 0 && (apart || !phi0_on_device);
+  int cur = 0;   // the plane that holds c (fused: after the first pass)
+  if (!fused) {
+    hipLaunchKernelGGL(k_ch_init, dim3(nb), dim3(256), 0, st, s, c[0], N);
     HIP_TRY(hipGetLastError());
-    cur = 1 - cur;
   }
-  float* dst = phi0_on_device ? phi0 : c[1 - cur];
-  hipLaunchKernelGGL(k_ch_final, dim3(nb), dim3(256), 0, st, c[cur], dst, N);
-  HIP_TRY(hipGetLastError());
-  if (!phi0_on_device)
-    HIP_TRY(hipMemcpyAsync(phi0, dst, (size_t)N * 4, hipMemcpyDeviceToHost, st));
+  for (int it = 0; it < iterations;) {
+    const bool first = fused && it == 0;
+    const int T = is3d ? 1 : std::min(kT2, iterations - it);
+    it += T;
+    const bool last = fused && it == iterations;
+    const int nxt = first ? 0 : 1 - cur;
+    float* out = last && phi0_on_device ? phi0 : c[nxt];
+    const uint8_t* img = first ? s : nullptr;
+    int rc;
+    if (is3d) rc = ch_pass3(G, c[cur], img, out, A, kap, dtM, last, st);
+    else if (T == 1) rc = ch_pass2<1>(G, c[cur], img, out, A, kap, dtM, last, st);
+    else if (T == 2) rc = ch_pass2<2>(G, c[cur], img, out, A, kap, dtM, last, st);
+    else if (T == 3) rc = ch_pass2<3>(G, c[cur], img, out, A, kap, dtM, last, st);
+    else rc = ch_pass2<4>(G, c[cur], img, out, A, kap, dtM, last, st);
+    if (rc) return rc;
+    cur = nxt;
+  }
+  const float* res = c[cur];
+  if (!fused) {
+    float* dst = phi0_on_device ? phi0 : c[1 - cur];
+    hipLaunchKernelGGL(k_ch_final, dim3(nb), dim3(256), 0, st, (const float*)c[cur], dst, N);
+    HIP_TRY(hipGetLastError());
+    res = dst;
+  }
+  if (!phi0_on_device) HIP_TRY(hipMemcpyAsync(phi0, res, pb, hipMemcpyDeviceToHost, st));
   if (!phi0_on_device || !solid_on_device) HIP_TRY(hipStreamSynchronize(st));
   return LBF_OK;
 }
