@@ -130,64 +130,75 @@ __global__ __launch_bounds__(256) void k3_lap_static(Geo3 G, float* stat, int N)
   stat[ST_LAP0 * (size_t)G.P + s] = 6.0f * lap;
 }
 
-// Equilibria of the initial state in post-stream form (tmp: the f, g, h
-// arrays); `in` holds phi (plane 0) and T (plane 1), linear, PL apart.
-__global__ __launch_bounds__(256) void k3_init_eq(Geo3 G, Phys ph, const float* stat,
-                                                  const float* in, float* tmp, int N) {
+// Chemical potential of the initial order parameter (no ice), linear.
+__global__ __launch_bounds__(256) void k3_init_mu(Geo3 G, Phys ph, const float* stat,
+                                                  const float* __restrict__ phi,
+                                                  float* __restrict__ mu, int N) {
   const int k = blockIdx.x * 256 + threadIdx.x;
   if (k >= N) return;
   int x, y, z;
   coords(G, k, x, y, z);
-  const size_t P = G.P, AS = G.AS;
+  const size_t P = G.P;
   const uint32_t s = sidx3(G, x, y, z);
-  const float pc = in[k];
+  const float pc = phi[k];
   float lap = 0.0f;
 #pragma unroll
   for (int i = 1; i < NQ; ++i) {
     const int xx = nb3(x + cx(i), G.n[0], G.per[0]), yy = nb3(y + cy(i), G.n[1], G.per[1]);
     const int zz = nb3(z + cz(i), G.n[2], G.per[2]);
-    lap += wgt(i) * (in[((size_t)zz * G.n[1] + yy) * G.n[0] + xx] - pc);
+    lap += wgt(i) * (phi[((size_t)zz * G.n[1] + yy) * G.n[0] + xx] - pc);
   }
-  lap *= 6.0f;
-  const float phi0 = stat[ST_PHI0 * P + s];
-  const float mu = lbf::chem_pot(ph, pc, lap, phi0, stat[ST_CTH * P + s], stat[ST_LAP0 * P + s],
-                                 0.0f, 0.0f);
-  const float C = lbf::clampf(0.5f * (1.0f - phi0 + pc), 0.0f, 1.0f);
-  const float Cp = lbf::clampf((C - ph.pcm_floor) * ph.inv_pcm_span, 0.0f, 1.0f);
-  const float chi = lbf::clampf(Cp, 0.0f, 1.0f - phi0);
-  const float Kliq = lbf::zeta(phi0, C, ph.rho_s, ph.rho_l, ph.rho_g) *
-                     lbf::zeta(phi0, C, ph.cp_s, ph.cp_l, ph.cp_g);
-  const float Tk = in[(size_t)G.PL + k];
-  const float rhoH = Kliq * (Tk - ph.T_m) + Kliq * ph.T_m + chi * ph.rho_l * ph.latent;
-  const float ET = ph.Eref * Tk;
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    tmp[i * P + s] = 0.0f;
-    tmp[AS + i * P + s] = (i == 0 ? pc : 0.0f) + (wgt(i) - (i == 0 ? 1.0f : 0.0f)) * mu;
-    tmp[2 * AS + i * P + s] = (i == 0) ? rhoH - ET + wgt(0) * ET : wgt(i) * ET;
-  }
+  mu[k] = lbf::chem_pot(ph, pc, 6.0f * lap, stat[ST_PHI0 * P + s], stat[ST_CTH * P + s],
+                        stat[ST_LAP0 * P + s], 0.0f, 0.0f);
 }
 
-// Inverse of the pull: post-collision populations whose pull gives `tmp`;
-// the rest populations become the high parts of their float-float storage.
-__global__ __launch_bounds__(256) void k3_unstream(Geo3 G, Phys ph, const float* tmp, float* dst,
-                                                   float* lag, int N) {
+// The initial state: post-collision populations whose pull gives the
+// equilibria of (phi, T) at rest, and zero lagged fields.  Population j of a node
+// is what its neighbour x + c_j pulls, w_j mu and w_j E_ref T of that neighbour
+// (the node's own across a wall); the rest populations are the high parts of
+// their float-float storage.  Written directly: forming the pulled state in a
+// buffer, clearing the lagged planes and streaming it back took 4.63 ms at 256^3
+// against 1.09 here.  The other buffer's velocity planes, which no step writes
+// without the flow-divergence source, are cleared too.
+__global__ __launch_bounds__(256) void k3_init_state(Geo3 G, Phys ph, const float* stat,
+                                                     const float* __restrict__ phi,
+                                                     const float* __restrict__ T,
+                                                     const float* __restrict__ mu,
+                                                     float* __restrict__ dst,
+                                                     float* __restrict__ lag,
+                                                     float* __restrict__ lag_other, int N) {
   const int k = blockIdx.x * 256 + threadIdx.x;
   if (k >= N) return;
   int x, y, z;
   coords(G, k, x, y, z);
   const size_t P = G.P, AS = G.AS;
   const size_t s = sidx3(G, x, y, z);
-  dst[s] = tmp[s];
-  lag[LAG_GHI * P + s] = tmp[AS + s];
-  lag[LAG_HHI * P + s] = tmp[2 * AS + s];
+  const float pc = phi[k], Tk = T[k], muk = mu[k], phi0 = stat[ST_PHI0 * P + s];
+  const float C = lbf::clampf(0.5f * (1.0f - phi0 + pc), 0.0f, 1.0f);
+  const float Cp = lbf::clampf((C - ph.pcm_floor) * ph.inv_pcm_span, 0.0f, 1.0f);
+  const float chi = lbf::clampf(Cp, 0.0f, 1.0f - phi0);
+  const float Kliq = lbf::zeta(phi0, C, ph.rho_s, ph.rho_l, ph.rho_g) *
+                     lbf::zeta(phi0, C, ph.cp_s, ph.cp_l, ph.cp_g);
+  const float rhoH = Kliq * (Tk - ph.T_m) + Kliq * ph.T_m + chi * ph.rho_l * ph.latent;
+  const float ET = ph.Eref * Tk;
+#pragma unroll
+  for (int j = 0; j < NLAG; ++j)
+    if (j != LAG_GHI && j != LAG_HHI) lag[j * P + s] = 0.0f;
+  lag[LAG_GHI * P + s] = pc + (wgt(0) - 1.0f) * muk;
+  lag[LAG_HHI * P + s] = rhoH - ET + wgt(0) * ET;
+  if (!ph.phi_src_flow)
+    for (int j = LAG_UX; j <= LAG_UZ; ++j) lag_other[j * P + s] = 0.0f;
+  dst[s] = 0.0f;
   dst[AS + s] = 0.0f;
   dst[2 * AS + s] = 0.0f;
+#pragma unroll
   for (int j = 1; j < NQ; ++j) {
-    // destination of population j leaving the node; the face of its wall
+    // destination of population j leaving the node; the face of its wall (the
+    // z face first, then y, then x)
     const int v[3] = {x + cx(j), y + cy(j), z + cz(j)};
     int d[3];
     int face = -1;
+#pragma unroll
     for (int a = 2; a >= 0; --a) {
       d[a] = v[a];
       if (v[a] < 0 || v[a] >= G.n[a]) {
@@ -195,17 +206,12 @@ __global__ __launch_bounds__(256) void k3_unstream(Geo3 G, Phys ph, const float*
         else if (face < 0) face = 2 * a + (v[a] < 0 ? 0 : 1);
       }
     }
-    if (face < 0) {
-      const size_t dk = sidx3(G, d[0], d[1], d[2]);
-      for (int b = 0; b < 3; ++b) dst[b * AS + j * P + s] = tmp[b * AS + j * P + dk];
-    } else {
-      const int i = opp(j);   // the population the node pulls back
-      dst[j * P + s] = tmp[i * P + s];
-      dst[AS + j * P + s] = tmp[AS + i * P + s];
-      const float hb = tmp[2 * AS + i * P + s];
-      dst[2 * AS + j * P + s] =
-          ((G.tmask >> face) & 1) ? 2.0f * wgt(i) * ph.Eref * G.Tw[face] - hb : hb;
-    }
+    const size_t kd = face < 0 ? ((size_t)d[2] * G.n[1] + d[1]) * G.n[0] + d[0] : (size_t)k;
+    dst[j * P + s] = 0.0f;
+    dst[AS + j * P + s] = wgt(j) * mu[kd];
+    float h = wgt(j) * (ph.Eref * T[kd]);
+    if (face >= 0 && ((G.tmask >> face) & 1)) h = 2.0f * wgt(j) * ph.Eref * G.Tw[face] - h;
+    dst[2 * AS + j * P + s] = h;
   }
 }
 
@@ -236,11 +242,11 @@ __global__ __launch_bounds__(256) void k3_moments(Geo3 G, Phys ph, BufArgs3 A, i
   st_rec(B.mom, (uint32_t)k * 16u, m.phi, m.fs, m.rho, lbf::ldp(B.lin, LAG_P, G.P, s));
 }
 
-// Step pass (READOUT = false) or read-out of the fields with FP64 block sums
-// (READOUT = true).
+// Step pass (READOUT = false) or read-out (READOUT = true): the fields, `stride`
+// floats apart (unless NULL), and FP64 block sums.
 template <bool READOUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k3_step(
-    Geo3 G, Phys ph, BufArgs3 A, float* fields, double* red, int N, int nblocks) {
+    Geo3 G, Phys ph, BufArgs3 A, float* fields, size_t stride, double* red, int N, int nblocks) {
   const int q = node_of_block(nblocks);
   const bool act = q < N;
   const int k = act ? node_in_strips(G, q) : q;
@@ -249,7 +255,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
     int x, y, z;
     coords(G, k, x, y, z);
     const Bufs3 B = make_bufs3(A, G);
-    const size_t PL = G.PL;
     Pull19 n;
     pull19(G, x, y, z, n);
     const int s = (int)(n.k4 >> 2);   // storage index of the node
@@ -293,8 +298,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                                      lbf::ldp(B.stat, ST_LAP0, G.P, s), m.fs, S.lfs);
       const float out[NFIELD] = {m.phi, m.T, 1.0f - m.fs, m.fs, o.u[0], o.u[1], o.u[2], o.p,
                                  m.rhoH, mu, m.C, m.chi, m.rho, m.ref_g + m.sg};
+      if (fields) {
 #pragma unroll
-      for (int f = 0; f < NFIELD; ++f) fields[f * PL + k] = out[f];
+        for (int f = 0; f < NFIELD; ++f) fields[f * stride + k] = out[f];
+      }
       const float um = sqrtf(o.u[0] * o.u[0] + o.u[1] * o.u[1] + o.u[2] * o.u[2]);
       v[0] = (double)m.ref_g + (double)m.sg;
       v[1] = (double)ref_h + (double)m.sh;
@@ -493,14 +500,6 @@ float* state_plane3(lbf3_sim* s, int c, int j) {
   return fp3(s, s->L.lag[c]) + (size_t)(j - NDIST) * s->L.P;
 }
 
-// Zero the lagged planes of state buffer c (every block).
-int zero_lags3(lbf3_sim* s, int c) {
-  const size_t w = NLAG * s->L.P * sizeof(float);
-  HIP_TRY(hipMemset2DAsync(fp3(s, s->L.lag[c]), s->L.nblk > 1 ? s->L.GS * sizeof(float) : w, 0, w,
-                           (size_t)s->L.nblk, s->stream));
-  return LBF_OK;
-}
-
 int copy3(lbf3_sim* s, void* dst, const void* src, size_t bytes, int on_device) {
   if (hipMemcpyAsync(dst, src, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                      s->stream) != hipSuccess)
@@ -510,17 +509,18 @@ int copy3(lbf3_sim* s, void* dst, const void* src, size_t bytes, int on_device) 
   return LBF_OK;
 }
 
-int launch_pair(lbf3_sim* s, bool readout) {
+// Both passes of a step, or of a read-out into `fields` (NULL: sums only).
+int launch_pair(lbf3_sim* s, bool readout, float* fields = nullptr, size_t stride = 0) {
   const int N = N3(s), nb = s->L.nblocks;
   BufArgs3 A = args3(s, s->cur);
   hipLaunchKernelGGL(k3_moments, dim3(nb), dim3(256), 0, s->stream, s->G, s->ph, A, N, nb);
   HIP_TRY(hipGetLastError());
   if (readout)
     hipLaunchKernelGGL((k3_step<true>), dim3(nb), dim3(256), 0, s->stream, s->G, s->ph, A,
-                       fp3(s, s->L.fields), reinterpret_cast<double*>(s->ws + s->L.red), N, nb);
+                       fields, stride, reinterpret_cast<double*>(s->ws + s->L.red), N, nb);
   else
     hipLaunchKernelGGL((k3_step<false>), dim3(nb), dim3(256), 0, s->stream, s->G, s->ph, A,
-                       (float*)nullptr, (double*)nullptr, N, nb);
+                       (float*)nullptr, (size_t)0, (double*)nullptr, N, nb);
   HIP_TRY(hipGetLastError());
   return LBF_OK;
 }
@@ -627,24 +627,25 @@ int lbf3_init_fields(lbf3_sim* s, const float* phi, const float* T, int32_t on_d
   if (!s || !phi || !T) return fail(LBF_EINVAL, "NULL argument");
   if (!s->have_geo) return fail(LBF_ESTATE, "lbf3_set_geometry must precede lbf3_init_fields");
   const size_t n = (size_t)N3(s);
+  // the read-out planes are free between calls: host fields are staged in the
+  // first two, the chemical potential goes to the third
   float* stage = fp3(s, s->L.fields);
-  int rc = copy3(s, stage, phi, n * sizeof(float), on_device);
-  if (rc) return rc;
-  rc = copy3(s, stage + s->L.PL, T, n * sizeof(float), on_device);
-  if (rc) return rc;
-  s->cur = 0;
-  float* tmp = fp3(s, s->L.dist[1]);
-  hipLaunchKernelGGL(k3_init_eq, dim3(s->L.nblocks), dim3(256), 0, s->stream, s->G, s->ph,
-                     (const float*)fp3(s, s->L.stat), (const float*)stage, tmp, N3(s));
-  HIP_TRY(hipGetLastError());
-  // both buffers' lagged planes start at zero, so a saved state does not
-  // depend on what the workspace held
-  for (int c = 0; c < 2; ++c) {
-    rc = zero_lags3(s, c);
+  if (!on_device) {
+    int rc = copy3(s, stage, phi, n * sizeof(float), 0);
     if (rc) return rc;
+    rc = copy3(s, stage + s->L.PL, T, n * sizeof(float), 0);
+    if (rc) return rc;
+    phi = stage;
+    T = stage + s->L.PL;
   }
-  hipLaunchKernelGGL(k3_unstream, dim3(s->L.nblocks), dim3(256), 0, s->stream, s->G, s->ph,
-                     (const float*)tmp, fp3(s, s->L.dist[0]), fp3(s, s->L.lag[0]), N3(s));
+  float* mu = stage + 2 * s->L.PL;
+  s->cur = 0;
+  hipLaunchKernelGGL(k3_init_mu, dim3(s->L.nblocks), dim3(256), 0, s->stream, s->G, s->ph,
+                     (const float*)fp3(s, s->L.stat), phi, mu, N3(s));
+  HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(k3_init_state, dim3(s->L.nblocks), dim3(256), 0, s->stream, s->G, s->ph,
+                     (const float*)fp3(s, s->L.stat), phi, T, (const float*)mu,
+                     fp3(s, s->L.dist[0]), fp3(s, s->L.lag[0]), fp3(s, s->L.lag[1]), N3(s));
   HIP_TRY(hipGetLastError());
   s->step = 0;
   s->have_init = true;
@@ -676,13 +677,16 @@ int lbf3_step(lbf3_sim* s, int32_t nsteps) {
 int lbf3_read_fields(lbf3_sim* s, float* dst, int32_t dst_on_device) {
   if (!s || !dst) return fail(LBF_EINVAL, "NULL argument");
   if (!s->have_init) return fail(LBF_ESTATE, "not initialised");
-  int rc = launch_pair(s, true);
-  if (rc) return rc;
   const size_t n = (size_t)N3(s);
-  for (int f = 0; f < NFIELD; ++f)
-    HIP_TRY(hipMemcpyAsync(dst + f * n, fp3(s, s->L.fields) + f * s->L.PL, n * sizeof(float),
-                           dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                           s->stream));
+  // into device memory the fields are written in place
+  float* F = dst_on_device ? dst : fp3(s, s->L.fields);
+  const size_t stride = dst_on_device ? n : s->L.PL;
+  int rc = launch_pair(s, true, F, stride);
+  if (rc) return rc;
+  if (!dst_on_device)
+    for (int f = 0; f < NFIELD; ++f)
+      HIP_TRY(hipMemcpyAsync(dst + f * n, F + f * stride, n * sizeof(float),
+                             hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
   return LBF_OK;
 }

@@ -141,7 +141,9 @@ struct Bufs {
   Rsrc lin;           // NLAG planes of the previous step
   Rsrc lout;          // NLAG planes, written by a step
   Rsrc stat;          // NSTAT planes
-  Rsrc fields;        // NFIELD planes (read-out mode)
+  Rsrc fields;        // read-out planes, or the moment planes of MODE_STEP_MOM
+  int fstride;        // floats between read-out planes
+  uint32_t fmask;     // bit f: read-out plane f is written
   const float* wallT; // 4 profiles, each `wstride` floats
   int wstride;
   double* red;        // per-block partial sums, NRED each
@@ -163,6 +165,9 @@ struct BufArgs {
   const float* wallT;
   int wstride;
   double* red;
+  int fstride;       // floats between the read-out planes (plane-major, >= nx ny
+                     // apart; 0 when a single field is read)
+  uint32_t fmask;    // read-out fields to write (bit per field)
 };
 
 // Bytes from a resource's base to the end of its array: the base holds
@@ -184,10 +189,13 @@ __device__ __forceinline__ Bufs make_bufs(const BufArgs& a, const Geo& G) {
   B.lin = make_rsrc(a.lin, block_extent(G, NLAG));
   B.lout = make_rsrc(a.lout, block_extent(G, NLAG));
   B.stat = make_rsrc(a.stat, block_extent(G, NSTAT));
-  // read-out planes (plane-major, PF apart), or the 3 moment planes of a
-  // recomputed step (state indexing, P apart)
-  const size_t fe = (NFIELD * (size_t)G.PF > 3 * P ? NFIELD * (size_t)G.PF : 3 * P) * 4u;
+  // read-out planes (plane-major, fstride apart; each nx ny floats), or the 3
+  // moment planes of a recomputed step (state indexing, P apart)
+  const size_t fr = (NFIELD - 1) * (size_t)a.fstride + (size_t)G.nx * G.ny;
+  const size_t fe = (fr > 3 * P ? fr : 3 * P) * 4u;
   B.fields = make_rsrc(a.fields, a.fields ? (uint32_t)fe : 0u);
+  B.fstride = a.fstride;
+  B.fmask = a.fmask;
   B.wallT = a.wallT;
   B.wstride = a.wstride;
   B.red = a.red;

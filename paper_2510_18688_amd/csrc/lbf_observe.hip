@@ -139,18 +139,8 @@ extern "C" {
 int lbf_profiles(lbf_sim* s, double* col, double* row, int32_t dst_on_device) {
   if (!s || !col || !row) return fail(LBF_EINVAL, "NULL argument");
   if (!s->have_init) return fail(LBF_ESTATE, "not initialised");
-  // read-out fields of the current state
-  BufArgs B{};
-  B.din = fptr(s, s->L.dist[s->cur]);
-  B.dout = fptr(s, s->L.dist[1 - s->cur]);
-  B.lin = fptr(s, s->L.lag[s->cur]);
-  B.lout = fptr(s, s->L.lag[1 - s->cur]);
-  B.stat = fptr(s, s->L.stat);
-  B.wallT = fptr(s, s->L.wall);
-  B.wstride = s->L.wstride;
-  B.fields = fptr(s, s->L.fields);
-  B.red = nullptr;
-  int rc = launch_step_args(s, MODE_FIELDS, false, B, s->stream);
+  // the two read-out fields that the profiles take, of the current state
+  int rc = launch_read_out(s, (1u << LBF_FIELD_FS) | (1u << LBF_FIELD_CHI), nullptr, 0);
   if (rc) return rc;
   const int nx = s->G.nx, ny = s->G.ny;
   const int nchunk = (ny + kProfileChunk - 1) / kProfileChunk;

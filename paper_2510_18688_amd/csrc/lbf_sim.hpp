@@ -106,6 +106,11 @@ namespace lbfi {
 inline float* fptr(lbf_sim* s, size_t off) { return reinterpret_cast<float*>(s->ws + off); }
 inline double* dptr(lbf_sim* s, size_t off) { return reinterpret_cast<double*>(s->ws + off); }
 
+// Read-out pass of the current state: the fields of `mask` (bit per field) into
+// `dst`, plane-major, `stride` floats apart (NULL: the workspace's read-out
+// planes).
+int launch_read_out(lbf_sim* s, uint32_t mask, float* dst, int stride);
+
 // Launch the step kernel (MODE_STEP, MODE_FIELDS or MODE_STEP_MOM) with the
 // simulation's tile shape on explicit buffers, on stream `st`.
 int launch_step_args(lbf_sim* s, int mode, bool red, lbf::BufArgs B, hipStream_t st);

@@ -425,21 +425,14 @@ __device__ __forceinline__ void step_strip(const Geo& G, const Phys& ph, const B
       } else {
         collide_node<false, MRT>(ph, cm, S, phi0, fin.cth, lap0, cQp, jxp, jyp, crh,
                                  fin.thold, fv, cg, ch, o);
-        // read-out planes are plane-major whatever the state's layout
-        const int kf = y * G.nx + x, PF = G.PF;
-        stp(B.fields, 0, PF, kf, cm.phi);
-        stp(B.fields, 1, PF, kf, cm.T);
-        stp(B.fields, 2, PF, kf, 1.0f - cm.fs);
-        stp(B.fields, 3, PF, kf, cm.fs);
-        stp(B.fields, 4, PF, kf, o.ux);
-        stp(B.fields, 5, PF, kf, o.uy);
-        stp(B.fields, 6, PF, kf, o.p);
-        stp(B.fields, 7, PF, kf, cm.rhoH);
-        stp(B.fields, 8, PF, kf, o.mu);
-        stp(B.fields, 9, PF, kf, cm.C);
-        stp(B.fields, 10, PF, kf, cm.chi);
-        stp(B.fields, 11, PF, kf, cm.rho);
-        stp(B.fields, 12, PF, kf, cm.ref_g + cm.sg);
+        // read-out planes are plane-major whatever the state's layout; only
+        // the fields asked for are written (none for a reduction)
+        const int kf = y * G.nx + x;
+        const float fld[NFIELD] = {cm.phi, cm.T,    1.0f - cm.fs, cm.fs, o.ux,   o.uy, o.p,
+                                   cm.rhoH, o.mu, cm.C, cm.chi, cm.rho, cm.ref_g + cm.sg};
+#pragma unroll
+        for (int f = 0; f < NFIELD; ++f)
+          if ((B.fmask >> f) & 1u) stp(B.fields, f, B.fstride, kf, fld[f]);
       }
       if (RED) {
         const float um = sqrtf(o.ux * o.ux + o.uy * o.uy);
