@@ -167,6 +167,7 @@ __global__ __launch_bounds__(256) void k3_init_state(Geo3 G, Phys ph, const floa
                                                      float* __restrict__ dst,
                                                      float* __restrict__ lag,
                                                      float* __restrict__ lag_other, int N) {
+#pragma clang fp contract(off)
   const int k = blockIdx.x * 256 + threadIdx.x;
   if (k >= N) return;
   int x, y, z;
@@ -179,13 +180,14 @@ __global__ __launch_bounds__(256) void k3_init_state(Geo3 G, Phys ph, const floa
   const float chi = lbf::clampf(Cp, 0.0f, 1.0f - phi0);
   const float Kliq = lbf::zeta(phi0, C, ph.rho_s, ph.rho_l, ph.rho_g) *
                      lbf::zeta(phi0, C, ph.cp_s, ph.cp_l, ph.cp_g);
-  const float rhoH = Kliq * (Tk - ph.T_m) + Kliq * ph.T_m + chi * ph.rho_l * ph.latent;
+  const float rhoH = __builtin_fmaf(
+      chi * ph.rho_l, ph.latent, __builtin_fmaf(Kliq, Tk - ph.T_m, Kliq * ph.T_m));
   const float ET = ph.Eref * Tk;
 #pragma unroll
   for (int j = 0; j < NLAG; ++j)
     if (j != LAG_GHI && j != LAG_HHI) lag[j * P + s] = 0.0f;
-  lag[LAG_GHI * P + s] = pc + (wgt(0) - 1.0f) * muk;
-  lag[LAG_HHI * P + s] = rhoH - ET + wgt(0) * ET;
+  lag[LAG_GHI * P + s] = __builtin_fmaf(wgt(0) - 1.0f, muk, pc);
+  lag[LAG_HHI * P + s] = __builtin_fmaf(wgt(0), ET, __builtin_fmaf(-ph.Eref, Tk, rhoH));
   if (!ph.phi_src_flow)
     for (int j = LAG_UX; j <= LAG_UZ; ++j) lag_other[j * P + s] = 0.0f;
   dst[s] = 0.0f;
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(256) void k3_init_state(Geo3 G, Phys ph, const floa
     dst[j * P + s] = 0.0f;
     dst[AS + j * P + s] = wgt(j) * mu[kd];
     float h = wgt(j) * (ph.Eref * T[kd]);
-    if (face >= 0 && ((G.tmask >> face) & 1)) h = 2.0f * wgt(j) * ph.Eref * G.Tw[face] - h;
+    if (face >= 0 && ((G.tmask >> face) & 1)) h = __builtin_fmaf(2.0f * wgt(j) * ph.Eref, G.Tw[face], -h);
     dst[2 * AS + j * P + s] = h;
   }
 }
@@ -332,25 +334,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
   }
 }
 
+// Fixed-order sum of per-block partials, one block of 256 threads per quantity.
 __global__ void k3_reduce_final(const double* part, int nblocks, double* out) {
   __shared__ double s[256];
-  for (int j = 0; j < kRed3; ++j) {
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-      const double t = part[(size_t)b * kRed3 + j];
-      v = (j == 4) ? fmax(v, t) : v + t;
-    }
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w)
-        s[threadIdx.x] = (j == 4) ? fmax(s[threadIdx.x], s[threadIdx.x + w])
-                                  : s[threadIdx.x] + s[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[j] = s[0];
+  const int j = blockIdx.x;
+  double v = 0.0;
+  for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+    const double t = part[(size_t)b * kRed3 + j];
+    v = (j == 4) ? fmax(v, t) : v + t;
+  }
+  s[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w)
+      s[threadIdx.x] = (j == 4) ? fmax(s[threadIdx.x], s[threadIdx.x + w])
+                                : s[threadIdx.x] + s[threadIdx.x + w];
     __syncthreads();
   }
+  if (threadIdx.x == 0) out[j] = s[0];
 }
 
 // Every byte offset a kernel forms fits 32 bits: 19 planes of the
@@ -697,7 +698,7 @@ int lbf3_reduce(lbf3_sim* s, double* out) {
   int rc = launch_pair(s, true);
   if (rc) return rc;
   double* fin = reinterpret_cast<double*>(s->ws + s->L.redfinal);
-  hipLaunchKernelGGL(k3_reduce_final, dim3(1), dim3(256), 0, s->stream,
+  hipLaunchKernelGGL(k3_reduce_final, dim3(kRed3), dim3(256), 0, s->stream,
                      (const double*)(s->ws + s->L.red), s->L.nblocks, fin);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipMemcpyAsync(s->host_red, fin, kRed3 * sizeof(double), hipMemcpyDeviceToHost,

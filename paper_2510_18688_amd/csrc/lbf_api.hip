@@ -237,6 +237,7 @@ __global__ void k_init_state(Geo G, Phys ph, const float* stat, const float* __r
                              float* __restrict__ dst, float* __restrict__ lag,
                              float* __restrict__ lag_other, const float* __restrict__ wallT,
                              int wstride) {
+#pragma clang fp contract(off)
   const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
   if (x >= G.nx || y >= G.ny) return;
   const long long P = G.P;
@@ -247,10 +248,12 @@ __global__ void k_init_state(Geo G, Phys ph, const float* stat, const float* __r
   const float chi = clampf(Cp, 0.0f, 1.0f - phi0);
   const float Kliq = zeta(phi0, C, ph.rho_s, ph.rho_l, ph.rho_g) *
                      zeta(phi0, C, ph.cp_s, ph.cp_l, ph.cp_g);
-  const float rhoH = Kliq * (Tk - ph.T_m) + Kliq * ph.T_m + chi * ph.rho_l * ph.latent;
+  const float rhoH = __builtin_fmaf(
+      chi * ph.rho_l, ph.latent, __builtin_fmaf(Kliq, Tk - ph.T_m, Kliq * ph.T_m));
   const float ET = ph.Eref * Tk;
   // rest populations as float-float: 16-bit high parts in one plane
-  const float g0 = pc + (wgt(0) - 1.0f) * muk, h0 = rhoH - ET + wgt(0) * ET;
+  const float g0 = __builtin_fmaf(wgt(0) - 1.0f, muk, pc);
+  const float h0 = __builtin_fmaf(wgt(0), ET, __builtin_fmaf(-ph.Eref, Tk, rhoH));
   const float gh = hi16(g0), hh = hi16(h0);
   dst[9 * P + k] = g0 - gh;
   dst[18 * P + k] = h0 - hh;
@@ -277,7 +280,7 @@ __global__ void k_init_state(Geo G, Phys ph, const float* stat, const float* __r
     dst[(9 + j) * P + k] = wgt(j) * mu[kd];
     float h = wgt(j) * (ph.Eref * T[kd]);
     if (wall >= 0 && ((G.tmask >> wall) & 1))
-      h = 2.0f * wgt(j) * ph.Eref * wallT[wall * wstride + (wall < 2 ? x : y)] - h;
+      h = __builtin_fmaf(2.0f * wgt(j) * ph.Eref, wallT[wall * wstride + (wall < 2 ? x : y)], -h);
     dst[(18 + j) * P + k] = h;
   }
 }
@@ -345,26 +348,26 @@ __global__ void k_unstream(Geo G, Phys ph, const float* tmp, float* dst, float* 
   }
 }
 
-// Fixed-order sum of per-block partials (one block of 256 threads).
+// Fixed-order sum of per-block partials: one block of 256 threads per quantity
+// (one block for all of them, one after the other, took 10.6 us for 96 partials
+// and 40 us for 16384).
 __global__ void k_reduce_blocks(const double* part, int nblocks, double* out) {
   __shared__ double s[256];
-  for (int j = 0; j < NRED; ++j) {
-    double v = (j == 4) ? 0.0 : 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-      const double t = part[(size_t)b * NRED + j];
-      v = (j == 4) ? fmax(v, t) : v + t;
-    }
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w)
-        s[threadIdx.x] = (j == 4) ? fmax(s[threadIdx.x], s[threadIdx.x + w])
-                                  : s[threadIdx.x] + s[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[j] = s[0];
+  const int j = blockIdx.x;
+  double v = 0.0;
+  for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+    const double t = part[(size_t)b * NRED + j];
+    v = (j == 4) ? fmax(v, t) : v + t;
+  }
+  s[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w)
+      s[threadIdx.x] = (j == 4) ? fmax(s[threadIdx.x], s[threadIdx.x + w])
+                                : s[threadIdx.x] + s[threadIdx.x + w];
     __syncthreads();
   }
+  if (threadIdx.x == 0) out[j] = s[0];
 }
 
 // Measurement aid: the step kernel's HBM access pattern without its
@@ -548,7 +551,7 @@ int check_stable(lbf_sim* s, const double* part, long long level) {
   dim3 grid;
   const int nb = grid_blocks(s, grid);
   double* fin = dptr(s, s->L.redfinal) + NRED;
-  hipLaunchKernelGGL(k_reduce_blocks, dim3(1), dim3(256), 0, s->stream, part, nb, fin);
+  hipLaunchKernelGGL(k_reduce_blocks, dim3(NRED), dim3(256), 0, s->stream, part, nb, fin);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipMemcpyAsync(s->host_red + NRED, fin, NRED * sizeof(double), hipMemcpyDeviceToHost,
                          s->stream));
@@ -845,11 +848,11 @@ int lbf_reduce(lbf_sim* s, double* out) {
   dim3 grid;
   const int nb = grid_blocks(s, grid);
   double* fin = dptr(s, s->L.redfinal);
-  hipLaunchKernelGGL(k_reduce_blocks, dim3(1), dim3(256), 0, s->stream,
+  hipLaunchKernelGGL(k_reduce_blocks, dim3(NRED), dim3(256), 0, s->stream,
                      (const double*)dptr(s, s->L.red[1]), nb, fin + NRED);
   HIP_TRY(hipGetLastError());
   if (s->have_budget) {
-    hipLaunchKernelGGL(k_reduce_blocks, dim3(1), dim3(256), 0, s->stream,
+    hipLaunchKernelGGL(k_reduce_blocks, dim3(NRED), dim3(256), 0, s->stream,
                        (const double*)dptr(s, s->L.red[0]), s->budget_blocks, fin);
     HIP_TRY(hipGetLastError());
   }
