@@ -496,11 +496,18 @@ struct Post {
 // When `collide` is false only the diagnostics are filled.
 // MRT: compile the MRT branches (taken when ph.mrt is set); BGK-only
 // simulations run the instantiation without them.
-template <bool COLLIDE, bool MRT = false>
+// `late` may fill gv and hv when they are needed first (after the flow's
+// collision and after the phase field's) instead of before the call.
+struct NothingLate {
+  __device__ __forceinline__ void phase(float*) const {}
+  __device__ __forceinline__ void enthalpy(float*) const {}
+};
+template <bool COLLIDE, bool MRT = false, class Late = NothingLate>
 __device__ __forceinline__ void collide_node(const Phys& ph, const Mom& m, const Stencil& S,
                                              float phi0, float cth, float lap_phi0, float Q_prev,
                                              float jx_prev, float jy_prev, float ref_h, float thold,
-                                             float* fv, float* gv, float* hv, Post& o) {
+                                             float* fv, float* gv, float* hv, Post& o,
+                                             const Late& late = Late()) {
   // isotropic stencils (factor 1/c_s^2 = 3 for the gradient, 2/c_s^2 = 6 for
   // the Laplacian)
   float gphx = 0, gphy = 0, lphi = 0, lfs = 0, grx = 0, gry = 0, gpx = 0, gpy = 0;
@@ -609,6 +616,7 @@ __device__ __forceinline__ void collide_node(const Phys& ph, const Mom& m, const
                dq * (1.0f / 12.0f) * (mrt_qx(i) * d[3] + mrt_qy(i) * d[4]);
   }
   // phase field (Sec. 3.2)
+  late.phase(gv);
   const float inv_tau_g = ph.inv_tau_g;
   const float pg = ph.pg;
   const float djx = jx - jx_prev, djy = jy - jy_prev;
@@ -655,6 +663,7 @@ __device__ __forceinline__ void collide_node(const Phys& ph, const Mom& m, const
   // renormalise g_0 = hi + lo (16-bit hi, FP32 lo)
   renorm16(m.ref_g, gv[0], o.ghi, gv[0]);
   // enthalpy, TRT (Sec. 3.3, eq22)
+  late.enthalpy(hv);
   const float ET = ph.Eref * T;
   const float cT = rhocp * T;
   // The equilibria must sum to rho H.  In FP32, (1 - w_0) rho_ref C_p,ref T

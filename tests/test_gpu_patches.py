@@ -1,0 +1,68 @@
+"""Steps taken in pairs on patches (needs a device): the same bits as one step a
+call, which marches strips, at the patches' edges (24 x 8 nodes each), on lattices
+smaller than one, with every kind of side, and around checking steps."""
+
+import copy
+import functools
+
+import pytest
+
+from paper_2510_18688_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lbf_mod():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2510_18688_amd import lbf
+    lbf.load()
+    return lbf
+
+
+def _slab(nx, ny, px, py):
+    case = W.slab_drop(nx, ny, 0.3 * min(nx, ny), 75.0, -1.0, h_s=min(4.0, 0.4 * ny))
+    case.periodic_x, case.periodic_y = px, py
+    return case
+
+
+@functools.lru_cache(None)
+def _walls():
+    return W.porous_medium(nx=131, ny=67, seed=5, rmin=6.0, rmax=10.0, porosity=0.8)
+
+
+CASES = {
+    "one_node": lambda: _slab(1, 1, True, False),
+    "one_node_periodic": lambda: _slab(1, 1, True, True),
+    "smaller_periodic": lambda: _slab(5, 3, True, True),
+    "one_patch": lambda: _slab(24, 8, True, False),
+    "one_patch_walls": lambda: _slab(24, 8, False, False),
+    "one_over": lambda: _slab(25, 9, True, True),
+    "one_under": lambda: _slab(47, 23, False, True),
+    "thin": lambda: _slab(130, 1, True, False),
+    "walls": lambda: copy.deepcopy(_walls()),
+    "pairs_alone": lambda: _slab(220, 900, True, False),   # odd steps go to strips
+}
+
+
+@pytest.mark.parametrize("mdot,mrt", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("rb,check", [(0, 0), (4, 3)])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_pairs_of_steps(lbf_mod, name, rb, check, mdot, mrt):
+    import torch
+    case = CASES[name]()
+    case.mat.phi_src_mdot = mdot
+    if mrt:
+        case.mat.mrt, case.mat.s_b, case.mat.s_q, case.mat.s_g = 1, 1.5, 1.2, 1.4
+    a = lbf_mod.Sim(case, row_block=rb, check_every=check)
+    b = lbf_mod.Sim(case, row_block=rb, check_every=0)
+    sa = torch.empty(a.state_bytes(), dtype=torch.uint8, device="cuda")
+    sb = torch.empty_like(sa)
+    for steps in (2, 3, 6, 11):
+        a.step(steps)
+        for _ in range(steps):
+            b.step(1)
+        a.save_state(sa)
+        b.save_state(sb)
+        assert torch.equal(sa, sb), steps
