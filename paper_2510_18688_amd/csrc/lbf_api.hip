@@ -483,18 +483,16 @@ int lbfi::launch_read_out(lbf_sim* s, uint32_t mask, float* dst, int stride) {
 
 namespace {
 
-// Steps are taken two at a time on patches where that makes at most this many of
-// them (1.5 million nodes; counted in patches because a lattice a few nodes thin
-// leaves most of each unused).  Above, a strip has rows enough to march, and the
-// nodes that neighbouring patches compute twice cost more than the state's second
-// trip through memory.  us a step, strips at their best tile against patches:
-// 128 x 96 14.2, 6.1; 256^2 15.7, 8.1; 640 x 480 36.5, 22.3; 1024^2 68, 61;
-// 1400 x 1000 121, 89; 2048 x 1024 122, 129; 2048^2 232, 258.
-constexpr long long kPatches = 8000;
-// A step left over by the pairs is taken on patches alone up to this many (one step
-// a launch, strips against patches: 128 x 96 14.2, 9.8; 455 x 318 23.3, 18.4; 512^2
-// 25.0, 32.0).
-constexpr long long kPatches1 = 1000;
+// Steps are taken two at a time on patches of the lattice, unless it is too thin to
+// fill a patch's rows or a third of its columns.  us a step, strips at their best tile
+// against patches, in the layout of rows in blocks of four: 128 x 96 14.2, 5.5; 256^2
+// 15.7, 7.7; 640 x 480 36.5, 19.5; 1000 x 700 64, 36; 1400 x 1000 121, 78; 2500 x 1500
+// 365, 189; 2048^2 233, 201; 4096 x 2048 452, 404.
+constexpr int kPatchLeast = 8;
+// A step left over by the pairs is taken on patches alone up to this many of them (one
+// step a launch, strips against patches: 512^2 25, 20; 1000 x 700 64, 44; 1400 x 1000
+// 121, 102; 2048 x 1024 122, 144).
+constexpr long long kPatches1 = 8000;
 
 // Patches of `steps` steps that the lattice takes, along x and y.
 long long patches_of(const lbf_sim* s, int steps, int* along_x = nullptr) {
@@ -504,19 +502,29 @@ long long patches_of(const lbf_sim* s, int steps, int* along_x = nullptr) {
   return (long long)nbx * ((s->G.ny + wy - 1) / wy);
 }
 
-// K steps (at most kPatchSteps) of the current state into the other buffers.
-int launch_patches(const lbf_sim* s, BufArgs B, int K) {
+}  // namespace
+
+bool lbfi::takes_patches(const lbf_sim* s) {
+  return s->G.nx >= kPatchLeast && s->G.ny >= kPatchLeast;
+}
+
+int lbfi::launch_patches(const lbf_sim* s, BufArgs B, int K, hipStream_t st, size_t state_stride,
+                         size_t mom_stride) {
   int nbx = 0;
   const dim3 grid((unsigned)patches_of(s, K, &nbx)), block(kPatchX * kPatchY);
-  if (s->ph.mrt)
-    hipLaunchKernelGGL(patch_kernel<true>, grid, block, 0, s->stream, s->G, s->ph, B, K, nbx);
+  const PatchRecord rec{state_stride, mom_stride};
+  if (state_stride)
+    hipLaunchKernelGGL((patch_kernel<false, true>), grid, block, 0, st, s->G, s->ph, B, rec, K,
+                       nbx);
+  else if (s->ph.mrt)
+    hipLaunchKernelGGL((patch_kernel<true, false>), grid, block, 0, st, s->G, s->ph, B, rec, K,
+                       nbx);
   else
-    hipLaunchKernelGGL(patch_kernel<false>, grid, block, 0, s->stream, s->G, s->ph, B, K, nbx);
+    hipLaunchKernelGGL((patch_kernel<false, false>), grid, block, 0, st, s->G, s->ph, B, rec, K,
+                       nbx);
   HIP_TRY(hipGetLastError());
   return LBF_OK;
 }
-
-}  // namespace
 
 int lbfi::launch_step_args(lbf_sim* s, int mode, bool red, BufArgs B, hipStream_t st) {
   switch (s->tile_x) {
@@ -811,17 +819,17 @@ int lbf_step(lbf_sim* s, int32_t nsteps) {
   if (nsteps == 0) return LBF_OK;
   if (s->timing) HIP_TRY(hipEventRecord(s->ev0, s->stream));
   const int k = s->prm.check_every;
-  const long long patches = patches_of(s, kPatchSteps);
+  const bool patches = takes_patches(s), single = patches_of(s, kPatchSteps) <= kPatches1;
   for (int it = 0; it < nsteps; ++it) {
     const bool last = it == nsteps - 1;
     // a checking step reduces the state it reads (time level s->step)
     const bool chk = k > 0 && s->step % k == 0;
-    if (patches <= kPatches && !last && !chk) {
+    if (patches && !last && !chk) {
       // up to the next step that reduces its state
       int K = 1;
       while (K < kPatchSteps && it + K < nsteps - 1 && !(k > 0 && (s->step + K) % k == 0)) ++K;
-      if (K == kPatchSteps || patches <= kPatches1) {
-        int rc = launch_patches(s, make_args(s), K);
+      if (K == kPatchSteps || single) {
+        int rc = launch_patches(s, make_args(s), K, s->stream);
         if (rc) return rc;
         s->cur = 1 - s->cur;
         s->step += K;

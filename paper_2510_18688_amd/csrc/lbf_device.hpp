@@ -217,9 +217,10 @@ __device__ __forceinline__ float lda(Rsrc r, uint32_t elem) {
 // on the D3Q19 passes; no policy, SC0 or SC0 + NT were 3-5 % slower.  The
 // stored values and every result are the same bits under each policy.
 constexpr int kStorePolicy = 16 | 2;
+template <int POLICY = kStorePolicy>
 __device__ __forceinline__ void stp(Rsrc r, int plane, int P, int k, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (uint32_t)k * 4u,
-                                        (uint32_t)plane * (uint32_t)P * 4u, kStorePolicy);
+                                        (uint32_t)plane * (uint32_t)P * 4u, POLICY);
 }
 
 // Reciprocal with the hardware approximation (1 ulp), used for every per-node

@@ -1,29 +1,36 @@
 // Coupled steps on patches: one or two steps of a patch of the lattice per
 // workgroup, one node per lane, the state in registers and LDS between them.
 //
-// A strip (step_strip) forms the moments of a row from three rows of loads and
-// waits for memory once per row; below about a million nodes it has too few rows
-// to march for that to be hidden, and every step pays a launch, a first wait and
-// the halo rows' moments.  A patch loads the post-collision state of its TX x TY
-// nodes once, every lane its own node (no shifted loads), and from then on
-// streams through LDS: the moving populations are exchanged there, then the
-// moments the stencils take.  Each step uses up two rings of nodes (the pull
-// reaches one node, the stencil of pulled moments another), so K steps deliver
-// the inner (TX - 4 K) x (TY - 4 K) nodes; the rings are computed by the
-// neighbouring patches as well.
+// A strip (step_strip) forms the moments of a row from three rows of loads, waits for
+// memory once per row, and writes and reads the whole state once per step; below about
+// a million nodes it has too few rows to march for the waits to be hidden, and on a
+// lattice whose rows are not a multiple of the memory's lines each access is split.
+// A patch loads the post-collision state of its TX x TY nodes once, every lane its own
+// node (no shifted loads), and from then on streams through LDS: the moving
+// populations are exchanged there, then the moments the stencils take.  Each step uses
+// up two rings of nodes (the pull reaches one node, the stencil of pulled moments
+// another), so K steps deliver the inner (TX - 4 K) x (TY - 4 K) nodes; the rings are
+// computed by the neighbouring patches as well.
 //
-// What bounds it is the instructions of the nodes computed twice (at 32 x 16 and two
-// steps 1.67 collisions and 2.33 pulls per node and step delivered); a row of wholly
-// outer nodes is skipped.  At 1400 x 1000 a step takes 89 us against 121 of strips and
-// 83 of the state's traffic for one step at 6.2 TB/s (halved here); 32 x 32 patches,
-// with less computed twice but one to a compute unit and so nothing beside the
-// barriers, take 114, 16 x 16 135, 24 x 24 168.
+// What bounds it is the vector instructions (78 % busy at 1400 x 1000), of the nodes
+// computed twice too: at 32 x 16 and two steps 1.67 collisions and 2.33 pulls per node
+// and step delivered, rows of wholly outer nodes skipped.  2048^2: 201 us a step
+// against 233 of strips and 187 of the state's traffic once at 6.2 TB/s (halved here).
+// Patches of 32 x 32 and 64 x 16 compute less twice, but one fills a compute unit and
+// nothing runs beside its barriers and loads (1400 x 1000: 99 and 95 us against 75).
 //
 // The same functions give the same bits as step_strip.
 #pragma once
 #include "lbf_step.hpp"
 
 namespace lbf {
+
+// Plain stores, not the strips' policy: a patch's rows are 24 nodes, so that the
+// cache puts the lines of neighbouring patches together, and a small state is found
+// there by the next launch (plain, non-temporal, SC1, both; us a step: 455 x 318 11.4,
+// 11.8, 11.1, 12.6; 1000 x 700 36.3, 40.3, 37.4, 45.3; 1400 x 1000 76, 76, 88, 89; a
+// recorded pair at 1024^2 145, 218, 171, 263).
+constexpr int kPatchPolicy = 0;
 
 template <int TX, int TY>
 struct PatchShared {
@@ -107,10 +114,19 @@ struct PatchLate {
   }
 };
 
-// Patch (bx, by) of the lattice, K steps.
-template <int TX, int TY, bool MRT>
-__device__ __forceinline__ void patch_steps(const Geo& G, const Phys& ph, const Bufs& B, int bx,
-                                            int by, int K, PatchShared<TX, TY>& sh) {
+// Where a recorded run's states and moments lie: the state of step s and the phi,
+// f_s, rho it was stepped from, `state` and `mom` floats apart (0: not recorded).
+struct PatchRecord {
+  size_t state, mom;
+};
+
+// Patch (bx, by) of the lattice, K steps of the state in A.  Stores the last step's
+// state, or with RECORD every step's, and the moments each was stepped from.
+template <int TX, int TY, bool MRT, bool RECORD>
+__device__ __forceinline__ void patch_steps(const Geo& G, const Phys& ph, BufArgs A,
+                                            PatchRecord rec, int bx, int by, int K,
+                                            PatchShared<TX, TY>& sh) {
+  const Bufs B = make_bufs(A, G);
   constexpr int N = TX * TY;
   const int t = threadIdx.x;
   const int lx = t % TX, ly = t / TX;
@@ -174,6 +190,26 @@ __device__ __forceinline__ void patch_steps(const Geo& G, const Phys& ph, const 
     if (flow) {
       sh.u[0][t] = uxp;
       sh.u[1][t] = uyp;
+    }
+  };
+  // the nodes this patch delivers
+  const bool inner = act && own && ring >= 2 * K;
+  auto store = [&](const Bufs& B) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      stp<kPatchPolicy>(B.fout, i, P, k, fv[i]);
+      stp<kPatchPolicy>(B.gout, i, P, k, gv[i]);
+      stp<kPatchPolicy>(B.hout, i, P, k, hv[i]);
+    }
+    stp<kPatchPolicy>(B.lout, LAG_FS, P, k, fsp);
+    stp<kPatchPolicy>(B.lout, LAG_Q, P, k, Qp);
+    stp<kPatchPolicy>(B.lout, LAG_JX, P, k, jxp);
+    if (!flow) stp<kPatchPolicy>(B.lout, LAG_JY, P, k, jyp);
+    stp<kPatchPolicy>(B.lout, LAG_P, P, k, pp);
+    stp<kPatchPolicy>(B.lout, LAG_GHI, P, k, __builtin_bit_cast(float, pack_hi(ghi, hhi)));
+    if (flow) {
+      stp<kPatchPolicy>(B.lout, LAG_UX, P, k, uxp);
+      stp<kPatchPolicy>(B.lout, LAG_UY, P, k, uyp);
     }
   };
   if (act) publish();
@@ -255,43 +291,36 @@ __device__ __forceinline__ void patch_steps(const Geo& G, const Phys& ph, const 
         jyp = o.jy;
       }
     }
+    if (RECORD && inner) {
+      BufArgs C = A;
+      C.dout += s * rec.state;
+      C.lout += s * rec.state;
+      C.fields += s * rec.mom;
+      const Bufs D = make_bufs(C, G);
+      stp<kPatchPolicy>(D.fields, 0, P, k, m.phi);
+      stp<kPatchPolicy>(D.fields, 1, P, k, m.fs);
+      stp<kPatchPolicy>(D.fields, 2, P, k, m.rho);
+      store(D);
+    }
     if (s + 1 < K) {
       __syncthreads();
       if (collides) publish();
       __syncthreads();
     }
   }
-  if (act && own && ring >= 2 * K) {
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      stp(B.fout, i, P, k, fv[i]);
-      stp(B.gout, i, P, k, gv[i]);
-      stp(B.hout, i, P, k, hv[i]);
-    }
-    stp(B.lout, LAG_FS, P, k, fsp);
-    stp(B.lout, LAG_Q, P, k, Qp);
-    stp(B.lout, LAG_JX, P, k, jxp);
-    if (!flow) stp(B.lout, LAG_JY, P, k, jyp);
-    stp(B.lout, LAG_P, P, k, pp);
-    stp(B.lout, LAG_GHI, P, k, __builtin_bit_cast(float, pack_hi(ghi, hhi)));
-    if (flow) {
-      stp(B.lout, LAG_UX, P, k, uxp);
-      stp(B.lout, LAG_UY, P, k, uyp);
-    }
-  }
+  if (!RECORD && inner) store(B);
 }
 
 constexpr int kPatchX = 32, kPatchY = 16, kPatchSteps = 2;
 
 // 1D grid of nbx * nby patches; four wavefronts per SIMD (two patches per compute
 // unit) hold the registers to 128.
-template <bool MRT>
+template <bool MRT, bool RECORD = false>
 __global__ __launch_bounds__(kPatchX* kPatchY) __attribute__((amdgpu_waves_per_eu(4, 8))) void
-patch_kernel(Geo G, Phys ph, BufArgs A, int K, int nbx) {
+patch_kernel(Geo G, Phys ph, BufArgs A, PatchRecord rec, int K, int nbx) {
   __shared__ PatchShared<kPatchX, kPatchY> sh;
-  const Bufs B = make_bufs(A, G);
   const int t = xcd_tile(blockIdx.x, gridDim.x);
-  patch_steps<kPatchX, kPatchY, MRT>(G, ph, B, t % nbx, t / nbx, K, sh);
+  patch_steps<kPatchX, kPatchY, MRT, RECORD>(G, ph, A, rec, t % nbx, t / nbx, K, sh);
 }
 
 }  // namespace lbf

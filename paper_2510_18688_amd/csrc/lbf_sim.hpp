@@ -114,5 +114,12 @@ int launch_read_out(lbf_sim* s, uint32_t mask, float* dst, int stride);
 // Launch the step kernel (MODE_STEP, MODE_FIELDS or MODE_STEP_MOM) with the
 // simulation's tile shape on explicit buffers, on stream `st`.
 int launch_step_args(lbf_sim* s, int mode, bool red, lbf::BufArgs B, hipStream_t st);
+// Whether the lattice's steps are taken in pairs on patches.
+bool takes_patches(const lbf_sim* s);
+// One or two steps on patches from B's state into its other one; with a stride also
+// the state of the first of two and the moments of each, `state_stride` and
+// `mom_stride` floats apart (BGK only).
+int launch_patches(const lbf_sim* s, lbf::BufArgs B, int K, hipStream_t st,
+                   size_t state_stride = 0, size_t mom_stride = 0);
 
 }  // namespace lbfi

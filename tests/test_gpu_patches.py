@@ -42,7 +42,8 @@ CASES = {
     "one_under": lambda: _slab(47, 23, False, True),
     "thin": lambda: _slab(130, 1, True, False),
     "walls": lambda: copy.deepcopy(_walls()),
-    "pairs_alone": lambda: _slab(220, 900, True, False),   # odd steps go to strips
+    "eight": lambda: _slab(8, 8, True, True),   # fewer go to strips
+    "seven": lambda: _slab(7, 30, True, True),
 }
 
 
