@@ -18,6 +18,7 @@
 
 #include "lbf.h"
 #include "lbf_adjoint.hpp"
+#include "lbf_patch.hpp"
 #include "lbf_sim.hpp"
 
 using namespace lbf;
@@ -121,14 +122,16 @@ int copy_state_out(lbf_tape* t, float* dst) {
   return LBF_OK;
 }
 
-// Step state `in` to `out` with the step kernel, storing phi, f_s, rho of
-// `in` in `mom`, on stream `st`.
-int recompute_step(lbf_tape* t, const float* in, float* out, float* mom, hipStream_t st) {
+// Step state `in` `K` times (1, or 2 on patches) into the states from `out` on,
+// storing phi, f_s, rho of each state stepped from `mom` on, on stream `st`.
+int recompute_steps(lbf_tape* t, const float* in, float* out, float* mom, int K, hipStream_t st) {
   lbf_sim* s = t->sim;
   BufArgs B = state_args(t, in);
   B.dout = out;
   B.lout = out + NDIST * t->P;
   B.fields = mom;
+  // (strips against patches, us a step: 1024^2 99, 73; 256^2 at the default tile 89, 9)
+  if (takes_patches(s)) return launch_patches(s, B, K, st, kStatePlanes * t->P, 3 * t->P);
   return launch_step_args(s, MODE_STEP_MOM, false, B, st);
 }
 
@@ -140,11 +143,14 @@ int recompute_segment(lbf_tape* t, int sgi, bool buffer_used) {
   const int c = sgi * t->seg;
   const int L = std::min(t->seg, t->nsteps - c);
   if (buffer_used) HIP_TRY(hipStreamWaitEvent(t->rstream, t->ev_used[b], 0));
-  for (int j = 0; j < L; ++j) {
+  const int most = takes_patches(t->sim) ? kPatchSteps : 1;
+  for (int j = 0; j < L;) {
+    const int K = std::min(most, L - j);
     const float* in = j == 0 ? state_ptr(t, 0, sgi) : state_ptr(t, 1 + b, j - 1);
-    int rc = recompute_step(t, in, state_ptr(t, 1 + b, j), t->mom[b] + (size_t)j * 3 * t->P,
-                            t->rstream);
+    int rc = recompute_steps(t, in, state_ptr(t, 1 + b, j), t->mom[b] + (size_t)j * 3 * t->P, K,
+                             t->rstream);
     if (rc) return rc;
+    j += K;
   }
   HIP_TRY(hipEventRecord(t->ev_rec[b], t->rstream));
   return LBF_OK;

@@ -436,6 +436,28 @@ __device__ __forceinline__ void collide_reverse(const Phys& ph, const Mom& m, co
   st[AS_GPY] = a_gpy;
 }
 
+// Planes of one array, at most 27 to a resource so that every byte offset fits 32
+// bits, as for the state: a lane's 64-bit addresses were an eighth of k_adj_collide's
+// 2300 instructions and a seventh of k_adj_gather's.
+__device__ __forceinline__ Rsrc adj_planes(const float* p, int first, int planes, int P) {
+  return make_rsrc(p + (size_t)first * P, (uint32_t)planes * (uint32_t)P * 4u);
+}
+
+// (stored without the state's policy: the next kernel reads it back)
+__device__ __forceinline__ void adj_st(Rsrc r, int plane, int P, int k, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (uint32_t)k * 4u,
+                                        (uint32_t)plane * (uint32_t)P * 4u, 0);
+}
+
+// Adjoint of a time level's distributions.
+struct AdjD {
+  Rsrc f, g, h, s;   // nine planes each, then the two sums'
+};
+__device__ __forceinline__ AdjD adj_dist(const float* p, int P) {
+  return {adj_planes(p, 0, 9, P), adj_planes(p, 9, 9, P), adj_planes(p, 18, 9, P),
+          adj_planes(p, 27, 2, P)};
+}
+
 // Arguments of the adjoint of step n.
 struct AdjStepArgs {
   Geo G;
@@ -456,11 +478,10 @@ struct AdjStepArgs {
 // gathered through the transpose of step n + 1's pull.  Anti-bounce-back
 // links add their wall-temperature derivative to gwall (each wall entry is
 // reached from one node only).
-__device__ __forceinline__ void gather_pull_adjoint(const Geo& G, const Phys& ph,
-                                                    const float* __restrict__ lamD, int x, int y,
-                                                    double* gwall, int wstride, float* af,
-                                                    float* ag, float* ah) {
-  const size_t P = (size_t)G.P;
+__device__ __forceinline__ void gather_pull_adjoint(const Geo& G, const Phys& ph, const AdjD& lam,
+                                                    int x, int y, double* gwall, int wstride,
+                                                    float* af, float* ag, float* ah) {
+  const int P = G.P;
   const int k = y * G.nx + x;
   // every lane requests the five values of each slot first (source node and
   // plane chosen per lane, no branch around the loads), so the 45 loads are
@@ -474,13 +495,13 @@ __device__ __forceinline__ void gather_pull_adjoint(const Geo& G, const Phys& ph
     wmask |= (uint32_t)w << j;
     ymask |= (uint32_t)wy << j;
     // across a wall the node pulls slot j back as population opp(j)
-    const size_t r = w ? (size_t)k : (size_t)ty * G.nx + tx;
-    const int pj = w ? opp(j) : j;
-    vf[j] = lamD[pj * P + r];
-    vg[j] = lamD[(9 + pj) * P + r];
-    vsg[j] = lamD[AD_SG * P + r];
-    vh[j] = lamD[(18 + pj) * P + r];
-    vsh[j] = lamD[AD_SH * P + r];
+    const int r = w ? k : ty * G.nx + tx;
+    const uint32_t e = (uint32_t)(w ? opp(j) : j) * (uint32_t)P + (uint32_t)r;
+    vf[j] = lda(lam.f, e);
+    vg[j] = lda(lam.g, e);
+    vsg[j] = ldp(lam.s, AD_SG - 27, P, r);
+    vh[j] = lda(lam.h, e);
+    vsh[j] = ldp(lam.s, AD_SH - 27, P, r);
   }
 #pragma unroll
   for (int j = 0; j < 9; ++j) {
@@ -505,7 +526,7 @@ __global__ __launch_bounds__(256) void k_adj_collide(AdjStepArgs a) {
   const Geo& G = a.G;
   const Phys& ph = a.ph;
   const Bufs B = make_bufs(a.F, G);
-  const size_t P = (size_t)G.P;
+  const int P = G.P;
   const int k = y * G.nx + x;
   // forward recompute of the node
   NodeIn in;
@@ -515,34 +536,39 @@ __global__ __launch_bounds__(256) void k_adj_collide(AdjStepArgs a) {
   node_finish(ph, in, m, s4);
   FlowIn fl;
   flow_load(G, ph, B, x, y, fl);
+  const Rsrc mom = adj_planes(a.mom, 0, 3, P);
   Stencil S;
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
     const int xx = map_axis(x + cx(i), G.nx, G.px), yy = map_axis(y + cy(i), G.ny, G.py);
-    const size_t kk = (size_t)yy * G.nx + xx;
-    S.phi[i] = a.mom[kk];
-    S.fs[i] = a.mom[P + kk];
-    S.rho[i] = a.mom[2 * P + kk];
-    S.p[i] = a.F.lin[LAG_P * P + kk];
+    const int kk = yy * G.nx + xx;
+    S.phi[i] = ldp(mom, 0, P, kk);
+    S.fs[i] = ldp(mom, 1, P, kk);
+    S.rho[i] = ldp(mom, 2, P, kk);
+    S.p[i] = ldp(B.lin, LAG_P, P, kk);
   }
   // adjoint of what the node wrote
   float af[9], ag[9], ah[9], aL[NADJ_L];
-  gather_pull_adjoint(G, ph, a.lamD, x, y, a.gwall, a.F.wstride, af, ag, ah);
+  const Rsrc lamL = adj_planes(a.lamL, 0, NADJ_L, P);
+  gather_pull_adjoint(G, ph, adj_dist(a.lamD, P), x, y, a.gwall, a.F.wstride, af, ag, ah);
 #pragma unroll
-  for (int j = 0; j < NADJ_L; ++j) aL[j] = a.lamL[j * P + k];
+  for (int j = 0; j < NADJ_L; ++j) aL[j] = ldp(lamL, j, P, k);
   float loc[NLOC], st[NST], ajx = 0.0f, ajy = 0.0f, acth = 0.0f;
   collide_reverse(ph, m, S, in.phi0, fl.cth, fl.lap0, fl.f, in.h, af, ag, ah, aL, loc, st, ajx,
                   ajy, acth);
+  const AdjD out = adj_dist(a.outD, P);
+  const Rsrc outL = adj_planes(a.outL, 0, NADJ_L, P), sto = adj_planes(a.st, 0, NST, P),
+             jac = adj_planes(a.jac, 0, NJAC, P);
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
-    a.outD[i * P + k] = af[i];
-    a.outD[(9 + i) * P + k] = ag[i];
-    a.outD[(18 + i) * P + k] = ah[i];
+    adj_st(out.f, i, P, k, af[i]);
+    adj_st(out.g, i, P, k, ag[i]);
+    adj_st(out.h, i, P, k, ah[i]);
   }
 #pragma unroll
-  for (int j = 0; j < NST; ++j) a.st[j * P + k] = st[j];
-  a.outL[LAG_JX * P + k] = ajx;
-  a.outL[LAG_JY * P + k] = ajy;
+  for (int j = 0; j < NST; ++j) adj_st(sto, j, P, k, st[j]);
+  adj_st(outL, LAG_JX, P, k, ajx);
+  adj_st(outL, LAG_JY, P, k, ajy);
   // moment reverse: local part, then unit responses to phi, f_s and rho
   float jv[NJAC];
   moments_reverse(ph, m, in.phi0, in.fsp, loc, jv[0], jv[1], jv[2]);
@@ -555,7 +581,7 @@ __global__ __launch_bounds__(256) void k_adj_collide(AdjStepArgs a) {
     moments_reverse(ph, m, in.phi0, in.fsp, e, jv[3 + 3 * c], jv[4 + 3 * c], jv[5 + 3 * c]);
   }
 #pragma unroll
-  for (int q = 0; q < NJAC; ++q) a.jac[q * P + k] = jv[q];
+  for (int q = 0; q < NJAC; ++q) adj_st(jac, q, P, k, jv[q]);
   a.gcth[k] += (double)acth;
 }
 
@@ -588,18 +614,19 @@ __global__ __launch_bounds__(256) void k_adj_gather(AdjGatherArgs a) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
   if (x >= a.G.nx) return;
   const Geo& G = a.G;
-  const size_t P = (size_t)G.P;
+  const int P = G.P;
   const int k = y * G.nx + x;
-  const float* __restrict__ st = a.st;
+  const Rsrc st = adj_planes(a.st, 0, NST, P);
+  const Rsrc jac = adj_planes(a.jac, 0, NJAC, P);
   float dphi = 0.0f, dfs = 0.0f, drho = 0.0f, dp = 0.0f;
   // contribution of one source node s through link i
-  auto add = [&](int i, size_t s) {
+  auto add = [&](int i, int s) {
     const float w = wgt(i);
-    dphi += 3.0f * w * (cx(i) * st[AS_GPHX * P + s] + cy(i) * st[AS_GPHY * P + s]) +
-            6.0f * w * st[AS_LPHI * P + s];
-    dfs += 6.0f * w * st[AS_LFS * P + s];
-    drho += 3.0f * w * (cx(i) * st[AS_GRX * P + s] + cy(i) * st[AS_GRY * P + s]);
-    dp += 3.0f * w * (cx(i) * st[AS_GPX * P + s] + cy(i) * st[AS_GPY * P + s]);
+    dphi += 3.0f * w * (cx(i) * ldp(st, AS_GPHX, P, s) + cy(i) * ldp(st, AS_GPHY, P, s)) +
+            6.0f * w * ldp(st, AS_LPHI, P, s);
+    dfs += 6.0f * w * ldp(st, AS_LFS, P, s);
+    drho += 3.0f * w * (cx(i) * ldp(st, AS_GRX, P, s) + cy(i) * ldp(st, AS_GRY, P, s));
+    dp += 3.0f * w * (cx(i) * ldp(st, AS_GPX, P, s) + cy(i) * ldp(st, AS_GPY, P, s));
   };
   // first the first source of each link: one per link away from a wall,
   // requested by every lane (a valid node either way, the term dropped where
@@ -614,9 +641,9 @@ __global__ __launch_bounds__(256) void k_adj_gather(AdjGatherArgs a) {
   float t8[9][8];
 #pragma unroll
   for (int i = 1; i < 9; ++i) {
-    const size_t s = (size_t)(nys[i] > 0 ? vy[i][0] : y) * G.nx + (nxs[i] > 0 ? vx[i][0] : x);
+    const int s = (nys[i] > 0 ? vy[i][0] : y) * G.nx + (nxs[i] > 0 ? vx[i][0] : x);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) t8[i][q] = st[q * P + s];
+    for (int q = 0; q < 8; ++q) t8[i][q] = ldp(st, q, P, s);
   }
 #pragma unroll
   for (int i = 1; i < 9; ++i) {
@@ -633,22 +660,23 @@ __global__ __launch_bounds__(256) void k_adj_gather(AdjGatherArgs a) {
     if (nxs[i] > 1 || nys[i] > 1) {
       for (int b = 0; b < nys[i]; ++b)
         for (int c = 0; c < nxs[i]; ++c)
-          if (b > 0 || c > 0) add(i, (size_t)vy[i][b] * G.nx + vx[i][c]);
+          if (b > 0 || c > 0) add(i, vy[i][b] * G.nx + vx[i][c]);
     }
   }
   // the node's own value in its Laplacians (weights of the moving links: 5/9)
-  dphi -= 6.0f * (5.0f / 9.0f) * st[AS_LPHI * P + k];
-  dfs -= 6.0f * (5.0f / 9.0f) * st[AS_LFS * P + k];
+  dphi -= 6.0f * (5.0f / 9.0f) * ldp(st, AS_LPHI, P, k);
+  dfs -= 6.0f * (5.0f / 9.0f) * ldp(st, AS_LFS, P, k);
   float r[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q)
-    r[q] = a.jac[q * P + k] + a.jac[(3 + q) * P + k] * dphi + a.jac[(6 + q) * P + k] * dfs +
-           a.jac[(9 + q) * P + k] * drho;
-  a.outD[AD_SG * P + k] = r[0];
-  a.outD[AD_SH * P + k] = r[1];
-  a.outL[LAG_FS * P + k] = r[2];
-  a.outL[LAG_Q * P + k] = 0.5f * r[1];
-  a.outL[LAG_P * P + k] = dp;
+    r[q] = ldp(jac, q, P, k) + ldp(jac, 3 + q, P, k) * dphi + ldp(jac, 6 + q, P, k) * dfs +
+           ldp(jac, 9 + q, P, k) * drho;
+  const Rsrc outS = adj_planes(a.outD, 27, 2, P), outL = adj_planes(a.outL, 0, NADJ_L, P);
+  adj_st(outS, AD_SG - 27, P, k, r[0]);
+  adj_st(outS, AD_SH - 27, P, k, r[1]);
+  adj_st(outL, LAG_FS, P, k, r[2]);
+  adj_st(outL, LAG_Q, P, k, 0.5f * r[1]);
+  adj_st(outL, LAG_P, P, k, dp);
 }
 
 // Seed of the reverse sweep: d J / d (phi, T, f_s) of the final state's
