@@ -300,12 +300,14 @@ int lbf_copy_probe(lbf_sim* sim, int32_t launches, double* ms_per_launch,
 const char* lbf_last_error(void);
 void lbf_destroy(lbf_sim* sim);
 
-/* ---- batches: many lattices advanced by one persistent launch per step ----
+/* ---- batches: many lattices advanced by one launch per pair of steps ----
  * A batch groups n initialised simulations that share one HIP stream (the
- * simulations stay owned by the caller and must outlive the batch).  Each
- * step is one launch of a fixed grid (as many workgroups as fit on the device at once) that
- * walks the work list of every lattice's tiles; runs of 32 steps are
- * captured once in a HIP graph and replayed.  Every lattice is advanced
+ * simulations stay owned by the caller and must outlive the batch).  Two
+ * steps are one launch over the patches of every lattice; a step left over, and
+ * every step of a batch with a lattice fewer than 8 nodes thin, is one launch
+ * of a fixed grid (as many workgroups as fit on the device at once) that walks
+ * the work list of every lattice's tiles.  Runs of 32 steps are captured once
+ * in a HIP graph and replayed.  Every lattice is advanced
  * exactly as lbf_step would advance it (same arithmetic, bit-identical
  * states).  Budget tracking (the step budget entries of lbf_reduce) is not
  * kept for batched steps. */

@@ -1069,12 +1069,14 @@ struct lbf_batch {
   bool mrt;                      // some lattice uses MRT: launch the kernel with its branches
   int grid;                      // persistent workgroups
   InstDesc* d_desc;
+  int2* d_patches;               // patches of every lattice, none if some lattice is thin
+  int npatches;
   int2* d_items;
   int nitems;
   std::vector<InstDesc> h_desc;  // host copy (source of the uploads)
   std::vector<int> desc_cur;     // sims' parity the descriptors were built for
   bool built;                    // work list, grid and graph match the tile shape
-  hipGraphExec_t graph;          // kGraphSteps launches, parities alternating
+  hipGraphExec_t graph;          // kGraphSteps steps, parities alternating
   bool have_graph;
   hipStream_t capture;           // private stream the graph is recorded on (the
                                  // legacy default stream cannot be captured)
@@ -1086,6 +1088,7 @@ struct lbf_batch {
 namespace {
 
 constexpr int kGraphSteps = 32;
+static_assert(kGraphSteps % (2 * kPatchSteps) == 0, "a replay leaves every parity in place");
 
 void batch_free_graph(lbf_batch* b) {
   if (b->have_graph) (void)hipGraphExecDestroy(b->graph);
@@ -1115,6 +1118,7 @@ int batch_upload_desc(lbf_batch* b) {
     }
     d.CY = b->tile_y;
     d.nbx = (s->G.nx + b->tile_x - 1) / b->tile_x;
+    patches_of(s, kPatchSteps, &d.npx);
   }
   HIP_TRY(hipMemcpyAsync(b->d_desc, b->h_desc.data(), n * sizeof(InstDesc),
                          hipMemcpyHostToDevice, b->stream));
@@ -1140,6 +1144,15 @@ int batch_build(lbf_batch* b) {
     const int nby = (b->sims[i]->G.ny + b->tile_y - 1) / b->tile_y;
     for (int t = 0; t < nbx * nby; ++t) items.push_back(make_int2(i, t));
   }
+  // patches in the same order, where every lattice takes its steps on them
+  std::vector<int2> patches;
+  bool all = true;
+  for (lbf_sim* sm : b->sims) all = all && takes_patches(sm);
+  if (all)
+    for (int i : order) {
+      const int np = (int)patches_of(b->sims[i], kPatchSteps);
+      for (int t = 0; t < np; ++t) patches.push_back(make_int2(i, t));
+    }
   HIP_TRY(hipStreamSynchronize(b->stream));
   batch_free_graph(b);
   if (b->d_items) (void)hipFree(b->d_items);
@@ -1149,6 +1162,14 @@ int batch_build(lbf_batch* b) {
   HIP_TRY(hipMemcpyAsync(b->d_items, items.data(), items.size() * sizeof(int2),
                          hipMemcpyHostToDevice, b->stream));
   b->nitems = (int)items.size();
+  if (b->d_patches) (void)hipFree(b->d_patches);
+  b->d_patches = nullptr;
+  b->npatches = (int)patches.size();
+  if (all) {
+    HIP_TRY(hipMalloc((void**)&b->d_patches, patches.size() * sizeof(int2)));
+    HIP_TRY(hipMemcpyAsync(b->d_patches, patches.data(), patches.size() * sizeof(int2),
+                           hipMemcpyHostToDevice, b->stream));
+  }
   int dev = 0, ncu = 0, per_cu = 0;
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1189,7 +1210,19 @@ void batch_launch_wx(lbf_batch* b, int parity, hipStream_t st) {
                        (const InstDesc*)b->d_desc, (const int2*)b->d_items, b->nitems, parity);
 }
 
-int batch_launch(lbf_batch* b, int parity, hipStream_t st) {
+// `steps` steps of every lattice: one on strips, or two on patches.
+int batch_launch(lbf_batch* b, int steps, int parity, hipStream_t st) {
+  if (steps > 1) {
+    const dim3 grid(b->npatches), block(kPatchX * kPatchY);
+    if (b->mrt)
+      hipLaunchKernelGGL(batch_patch_kernel<true>, grid, block, 0, st, (const InstDesc*)b->d_desc,
+                         (const int2*)b->d_patches, parity);
+    else
+      hipLaunchKernelGGL(batch_patch_kernel<false>, grid, block, 0, st, (const InstDesc*)b->d_desc,
+                         (const int2*)b->d_patches, parity);
+    HIP_TRY(hipGetLastError());
+    return LBF_OK;
+  }
   switch (b->tile_x) {
     case 64: batch_launch_wx<64>(b, parity, st); break;
     case 128: batch_launch_wx<128>(b, parity, st); break;
@@ -1272,14 +1305,18 @@ int lbf_batch_step(lbf_batch* b, int32_t nsteps) {
     return fail(LBF_ENOMEM, "host allocation failed");
   }
   if (b->timing) HIP_TRY(hipEventRecord(b->ev0, b->stream));
+  // pairs of steps on patches (64 lattices 64 .. 512 wide: 270 us a step on
+  // strips, 188)
+  const int most = b->npatches > 0 ? kPatchSteps : 1;
   int done = 0;
   if (nsteps >= kGraphSteps) {
     if (!b->have_graph) {
-      // one graph of kGraphSteps persistent launches, parities alternating
+      // one graph of kGraphSteps steps, parities alternating
       hipGraph_t g = nullptr;
       HIP_TRY(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
       int rc = LBF_OK;
-      for (int k = 0; k < kGraphSteps && rc == LBF_OK; ++k) rc = batch_launch(b, k & 1, b->capture);
+      for (int k = 0; k < kGraphSteps / most && rc == LBF_OK; ++k)
+        rc = batch_launch(b, most, k & 1, b->capture);
       const hipError_t ec = hipStreamEndCapture(b->capture, &g);
       if (rc == LBF_OK && ec != hipSuccess)
         rc = fail(LBF_EHIP, "hipStreamEndCapture failed: %s", hipGetErrorString(ec));
@@ -1289,15 +1326,19 @@ int lbf_batch_step(lbf_batch* b, int32_t nsteps) {
       if (rc) return rc;
       b->have_graph = true;
     }
-    // kGraphSteps is even: each replay leaves every parity where it started
+    // an even number of launches: each replay leaves every parity where it started
     while (nsteps - done >= kGraphSteps) {
       HIP_TRY(hipGraphLaunch(b->graph, b->stream));
       done += kGraphSteps;
     }
   }
-  for (int k = 0; done < nsteps; ++k, ++done) {
-    int rc = batch_launch(b, k & 1, b->stream);
+  int parity = 0;
+  while (done < nsteps) {
+    const int n = std::min(most, nsteps - done);
+    int rc = batch_launch(b, n, parity, b->stream);
     if (rc) return rc;
+    parity ^= 1;
+    done += n;
   }
   if (b->timing) {
     HIP_TRY(hipEventRecord(b->ev1, b->stream));
@@ -1307,7 +1348,7 @@ int lbf_batch_step(lbf_batch* b, int32_t nsteps) {
     b->last_ms = ms / nsteps;
   }
   for (lbf_sim* s : b->sims) {
-    s->cur ^= nsteps & 1;
+    s->cur ^= parity;
     s->step += nsteps;
     s->have_budget = false;
   }
@@ -1330,6 +1371,7 @@ void lbf_batch_destroy(lbf_batch* b) {
   batch_free_graph(b);
   if (b->d_desc) (void)hipFree(b->d_desc);
   if (b->d_items) (void)hipFree(b->d_items);
+  if (b->d_patches) (void)hipFree(b->d_patches);
   if (b->ev0) (void)hipEventDestroy(b->ev0);
   if (b->ev1) (void)hipEventDestroy(b->ev1);
   if (b->capture) (void)hipStreamDestroy(b->capture);

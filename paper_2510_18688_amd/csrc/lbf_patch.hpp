@@ -323,4 +323,19 @@ patch_kernel(Geo G, Phys ph, BufArgs A, PatchRecord rec, int K, int nbx) {
   patch_steps<kPatchX, kPatchY, MRT, RECORD>(G, ph, A, rec, t % nbx, t / nbx, K, sh);
 }
 
+// The same on the lattices of a batch: one workgroup per (instance, patch) of the work
+// list, two steps.
+template <bool MRT>
+__global__ __launch_bounds__(kPatchX* kPatchY) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+batch_patch_kernel(const InstDesc* __restrict__ D, const int2* __restrict__ items, int parity) {
+  __shared__ PatchShared<kPatchX, kPatchY> sh;
+  const int2 item = items[xcd_tile(blockIdx.x, gridDim.x)];
+  const Geo G = D[item.x].G;
+  const Phys ph = D[item.x].ph;
+  const BufArgs A = D[item.x].A[parity];
+  const int nbx = D[item.x].npx;
+  patch_steps<kPatchX, kPatchY, MRT, false>(G, ph, A, PatchRecord{0, 0}, item.y % nbx,
+                                            item.y / nbx, kPatchSteps, sh);
+}
+
 }  // namespace lbf

@@ -509,6 +509,7 @@ struct InstDesc {
   Phys ph;
   BufArgs A[2];
   int CY, nbx;
+  int npx;   // patches along x
 };
 
 // Persistent batched step: a fixed grid walks the work list of (instance,

@@ -67,3 +67,35 @@ def test_pairs_of_steps(lbf_mod, name, rb, check, mdot, mrt):
         a.save_state(sa)
         b.save_state(sb)
         assert torch.equal(sa, sb), steps
+
+
+@pytest.mark.parametrize("thin", [False, True])
+@pytest.mark.parametrize("mrt", [0, 1])
+def test_batch_of_patches(lbf_mod, mrt, thin):
+    """Batched pairs against the lattices stepped alone, one step a call; a lattice
+    too thin for patches sends the whole batch to strips."""
+    import torch
+    names = ["walls", "eight", "one_over", "one_under"] + (["thin"] if thin else [])
+
+    def sims():
+        out = []
+        for i, name in enumerate(names):
+            case = CASES[name]()
+            case.mat.phi_src_mdot = i % 2
+            if mrt:
+                case.mat.mrt, case.mat.s_b, case.mat.s_q, case.mat.s_g = 1, 1.5, 1.2, 1.4
+            out.append(lbf_mod.Sim(case, row_block=(0, 4)[i % 2]))
+        return out
+
+    a, b = sims(), sims()
+    batch = lbf_mod.Batch(a)
+    for steps in (5, 37, 2, 70):
+        batch.step(steps)
+        for x, y in zip(a, b):
+            for _ in range(steps):
+                y.step(1)
+            sx = torch.empty(x.state_bytes(), dtype=torch.uint8, device="cuda")
+            sy = torch.empty_like(sx)
+            x.save_state(sx)
+            y.save_state(sy)
+            assert torch.equal(sx, sy), (steps, x.nx, x.ny, x.case.mat.mrt)
