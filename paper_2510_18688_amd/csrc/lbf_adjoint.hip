@@ -241,7 +241,8 @@ int lbf_tape_forward(lbf_tape* t) {
   for (int c = 0; c < t->nsteps; c += t->seg) {
     int rc = copy_state_out(t, state_ptr(t, 0, c / t->seg));
     if (rc) return rc;
-    rc = lbf_step(s, std::min(t->seg, t->nsteps - c));
+    const int n = std::min(t->seg, t->nsteps - c);
+    rc = advance(s, n, c + n == t->nsteps);   // the budget is the run's last step's
     if (rc) return rc;
   }
   t->recorded = true;

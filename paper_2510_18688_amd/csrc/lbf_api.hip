@@ -612,6 +612,57 @@ int check_stable(lbf_sim* s, const double* part, long long level) {
 
 }  // namespace
 
+int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
+  if (nsteps == 0) return LBF_OK;
+  if (s->timing) HIP_TRY(hipEventRecord(s->ev0, s->stream));
+  const int k = s->prm.check_every;
+  const bool patches = takes_patches(s), single = patches_of(s, kPatchSteps) <= kPatches1;
+  for (int it = 0; it < nsteps; ++it) {
+    const bool last = budget && it == nsteps - 1;
+    // a checking step reduces the state it reads (time level s->step)
+    const bool chk = k > 0 && s->step % k == 0;
+    if (patches && !last && !chk) {
+      // up to the next step that reduces its state
+      int K = 1;
+      const int end = budget ? nsteps - 1 : nsteps;
+      while (K < kPatchSteps && it + K < end && !(k > 0 && (s->step + K) % k == 0)) ++K;
+      if (K == kPatchSteps || single) {
+        int rc = launch_patches(s, make_args(s), K, s->stream);
+        if (rc) return rc;
+        s->cur = 1 - s->cur;
+        s->step += K;
+        it += K - 1;
+        continue;
+      }
+    }
+    double* rb = last ? dptr(s, s->L.red[0]) : (chk ? dptr(s, s->L.red[1]) : nullptr);
+    int rc = launch_step(s, MODE_STEP, last || chk, rb);
+    if (rc) return rc;
+    s->cur = 1 - s->cur;
+    s->step++;
+    if (chk) {
+      rc = check_stable(s, rb, s->step - 1);
+      if (rc) {
+        dim3 grid;
+        s->budget_blocks = grid_blocks(s, grid);
+        s->have_budget = last;
+        return rc;
+      }
+    }
+  }
+  if (s->timing) {
+    HIP_TRY(hipEventRecord(s->ev1, s->stream));
+    HIP_TRY(hipEventSynchronize(s->ev1));
+    float ms = 0.0f;
+    HIP_TRY(hipEventElapsedTime(&ms, s->ev0, s->ev1));
+    s->last_ms = ms / nsteps;
+  }
+  dim3 grid;
+  s->budget_blocks = grid_blocks(s, grid);
+  s->have_budget = budget;
+  return LBF_OK;
+}
+
 // ================================================================ C ABI
 extern "C" {
 
@@ -816,53 +867,7 @@ int lbf_step(lbf_sim* s, int32_t nsteps) {
   if (!s) return fail(LBF_EINVAL, "sim is NULL");
   if (nsteps < 0) return fail(LBF_EINVAL, "nsteps %d", nsteps);
   if (!s->have_init) return fail(LBF_ESTATE, "lbf_init_fields must precede lbf_step");
-  if (nsteps == 0) return LBF_OK;
-  if (s->timing) HIP_TRY(hipEventRecord(s->ev0, s->stream));
-  const int k = s->prm.check_every;
-  const bool patches = takes_patches(s), single = patches_of(s, kPatchSteps) <= kPatches1;
-  for (int it = 0; it < nsteps; ++it) {
-    const bool last = it == nsteps - 1;
-    // a checking step reduces the state it reads (time level s->step)
-    const bool chk = k > 0 && s->step % k == 0;
-    if (patches && !last && !chk) {
-      // up to the next step that reduces its state
-      int K = 1;
-      while (K < kPatchSteps && it + K < nsteps - 1 && !(k > 0 && (s->step + K) % k == 0)) ++K;
-      if (K == kPatchSteps || single) {
-        int rc = launch_patches(s, make_args(s), K, s->stream);
-        if (rc) return rc;
-        s->cur = 1 - s->cur;
-        s->step += K;
-        it += K - 1;
-        continue;
-      }
-    }
-    double* rb = last ? dptr(s, s->L.red[0]) : (chk ? dptr(s, s->L.red[1]) : nullptr);
-    int rc = launch_step(s, MODE_STEP, last || chk, rb);
-    if (rc) return rc;
-    s->cur = 1 - s->cur;
-    s->step++;
-    if (chk) {
-      rc = check_stable(s, rb, s->step - 1);
-      if (rc) {
-        dim3 grid;
-        s->budget_blocks = grid_blocks(s, grid);
-        s->have_budget = last;
-        return rc;
-      }
-    }
-  }
-  if (s->timing) {
-    HIP_TRY(hipEventRecord(s->ev1, s->stream));
-    HIP_TRY(hipEventSynchronize(s->ev1));
-    float ms = 0.0f;
-    HIP_TRY(hipEventElapsedTime(&ms, s->ev0, s->ev1));
-    s->last_ms = ms / nsteps;
-  }
-  dim3 grid;
-  s->budget_blocks = grid_blocks(s, grid);
-  s->have_budget = true;
-  return LBF_OK;
+  return advance(s, nsteps, true);
 }
 
 int lbf_read_fields(lbf_sim* s, float* dst, int32_t dst_on_device) {

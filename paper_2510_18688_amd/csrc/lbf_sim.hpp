@@ -114,6 +114,9 @@ int launch_read_out(lbf_sim* s, uint32_t mask, float* dst, int stride);
 // Launch the step kernel (MODE_STEP, MODE_FIELDS or MODE_STEP_MOM) with the
 // simulation's tile shape on explicit buffers, on stream `st`.
 int launch_step_args(lbf_sim* s, int mode, bool red, lbf::BufArgs B, hipStream_t st);
+// lbf_step; without `budget` the last step is like the others and leaves no step
+// budget for lbf_reduce.
+int advance(lbf_sim* s, int nsteps, bool budget);
 // Whether the lattice's steps are taken in pairs on patches.
 bool takes_patches(const lbf_sim* s);
 // One or two steps on patches from B's state into its other one; with a stride also
