@@ -724,8 +724,15 @@ int lbf_create(const lbf_params* params, void* stream, void* workspace, size_t w
     }
     s->owns_ws = true;
   }
-  s->tile_x = params->nx >= 128 ? 128 : 64;
-  s->tile_y = 32;
+  // Strips as wide as the widest measured, and so few rows that the device is full:
+  // 2048 wavefronts, two to a SIMD (us a step, 128 x 32 against this: 256^2 131, 16;
+  // 512^2 128, 25; 1024^2 122, 68; 2048^2 260, 233).  Never more than 32 rows, which a
+  // larger lattice gains nothing from.
+  s->tile_x = params->nx >= 256 ? 256 : (params->nx >= 128 ? 128 : 64);
+  const long long wave_rows = (long long)((params->nx + s->tile_x - 1) / s->tile_x) *
+                              (s->tile_x / 64) * params->ny;
+  s->tile_y = 1;
+  while (s->tile_y < 32 && s->tile_y * 2048LL < wave_rows) s->tile_y *= 2;
   if (hipHostMalloc((void**)&s->host_red, 2 * NRED * sizeof(double), hipHostMallocDefault) !=
           hipSuccess ||
       hipEventCreate(&s->ev0) != hipSuccess || hipEventCreate(&s->ev1) != hipSuccess) {
