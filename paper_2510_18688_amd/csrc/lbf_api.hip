@@ -483,7 +483,7 @@ int lbfi::launch_read_out(lbf_sim* s, uint32_t mask, float* dst, int stride) {
 
 namespace {
 
-// Steps are taken two at a time on patches of the lattice, unless it is too thin to
+// Steps are taken two (or three, below) at a time on patches of the lattice, unless it is too thin to
 // fill a patch's rows or a third of its columns.  us a step, strips at their best tile
 // against patches, in the layout of rows in blocks of four: 128 x 96 14.2, 5.5; 256^2
 // 15.7, 7.7; 640 x 480 36.5, 19.5; 1000 x 700 64, 36; 1400 x 1000 121, 78; 2500 x 1500
@@ -493,6 +493,12 @@ constexpr int kPatchLeast = 8;
 // step a launch, strips against patches: 512^2 25, 20; 1000 x 700 64, 44; 1400 x 1000
 // 121, 102; 2048 x 1024 122, 144).
 constexpr long long kPatches1 = 8000;
+
+// Three steps a launch where that leaves each compute unit at most one patch (20 x 4
+// nodes of one): the launch and its first loads are then most of a pair's time (two
+// against three, us a step: 64^2 5.4, 4.7; 128 x 96 5.4, 4.8; 160 x 120 5.5, 4.9; 200 x
+// 150, 375 patches, 5.7, 6.4).
+constexpr long long kPatches3 = 256;
 
 // Patches of `steps` steps that the lattice takes, along x and y.
 long long patches_of(const lbf_sim* s, int steps, int* along_x = nullptr) {
@@ -617,6 +623,7 @@ int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
   if (s->timing) HIP_TRY(hipEventRecord(s->ev0, s->stream));
   const int k = s->prm.check_every;
   const bool patches = takes_patches(s), single = patches_of(s, kPatchSteps) <= kPatches1;
+  const int most = patches_of(s, 3) <= kPatches3 ? 3 : kPatchSteps;
   for (int it = 0; it < nsteps; ++it) {
     const bool last = budget && it == nsteps - 1;
     // a checking step reduces the state it reads (time level s->step)
@@ -625,8 +632,8 @@ int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
       // up to the next step that reduces its state
       int K = 1;
       const int end = budget ? nsteps - 1 : nsteps;
-      while (K < kPatchSteps && it + K < end && !(k > 0 && (s->step + K) % k == 0)) ++K;
-      if (K == kPatchSteps || single) {
+      while (K < most && it + K < end && !(k > 0 && (s->step + K) % k == 0)) ++K;
+      if (K > 1 || single) {
         int rc = launch_patches(s, make_args(s), K, s->stream);
         if (rc) return rc;
         s->cur = 1 - s->cur;

@@ -1,4 +1,4 @@
-// Coupled steps on patches: one or two steps of a patch of the lattice per
+// Coupled steps on patches: one to three steps of a patch of the lattice per
 // workgroup, one node per lane, the state in registers and LDS between them.
 //
 // A strip (step_strip) forms the moments of a row from three rows of loads, waits for

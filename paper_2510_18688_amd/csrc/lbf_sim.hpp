@@ -119,8 +119,8 @@ int launch_step_args(lbf_sim* s, int mode, bool red, lbf::BufArgs B, hipStream_t
 int advance(lbf_sim* s, int nsteps, bool budget);
 // Whether the lattice's steps are taken in pairs on patches.
 bool takes_patches(const lbf_sim* s);
-// One or two steps on patches from B's state into its other one; with a stride also
-// the state of the first of two and the moments of each, `state_stride` and
+// One to three steps on patches from B's state into its other one; with a stride also
+// the state of every step and the moments of each, `state_stride` and
 // `mom_stride` floats apart (BGK only).
 int launch_patches(const lbf_sim* s, lbf::BufArgs B, int K, hipStream_t st,
                    size_t state_stride = 0, size_t mom_stride = 0);

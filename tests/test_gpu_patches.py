@@ -1,5 +1,6 @@
-"""Steps taken in pairs on patches (needs a device): the same bits as one step a
-call, which marches strips, at the patches' edges (24 x 8 nodes each), on lattices
+"""Steps taken two or three at a time on patches (needs a device): the same bits as
+one step a call, which marches strips, at the patches' edges (24 x 8 nodes each for
+two steps, 20 x 4 for three; up to 256 of these are taken), on lattices
 smaller than one, with every kind of side, and around checking steps."""
 
 import copy
@@ -42,6 +43,10 @@ CASES = {
     "one_under": lambda: _slab(47, 23, False, True),
     "thin": lambda: _slab(130, 1, True, False),
     "walls": lambda: copy.deepcopy(_walls()),
+    "three_steps": lambda: _slab(40, 12, True, False),
+    "three_steps_over": lambda: _slab(41, 13, False, True),
+    "most_three_steps": lambda: _slab(320, 64, True, False),
+    "too_many_for_three": lambda: _slab(321, 64, True, False),
     "eight": lambda: _slab(8, 8, True, True),   # fewer go to strips
     "seven": lambda: _slab(7, 30, True, True),
 }
