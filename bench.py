@@ -151,7 +151,7 @@ def cpu_baseline(case, seconds):
 
 
 def batched(lbf, W, torch, steps):
-    """64 uneven droplet lattices: one persistent launch per step (graph
+    """64 uneven droplet lattices: one launch per pair of steps (graph
     replays) against the same lattices stepped one after another with their
     own launches."""
     from paper_2510_18688_amd import autotune
@@ -520,7 +520,7 @@ def main():
         "pct_hbm": round(100.0 * mlups * 1e6 * BYTES_PER_LU / (HBM_PEAK_GBS * 1e9), 2),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "kernel": "step_kernel",
+                     "traffic": traffic, "kernel": "patch_kernel",
                      "kernel_ms": round(kms, 5), "bytes_per_lu": BYTES_PER_LU,
                      "impl_bytes_per_lu": IMPL_BYTES_PER_LU,
                      "impl_frac": round(IMPL_BYTES_PER_LU * nodes / (kms * 1e-3) / 1e9

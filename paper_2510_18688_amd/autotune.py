@@ -1,8 +1,9 @@
 """Launch-shape and plane-stride autotuner of the step kernel.
 
-For a lattice size it times every candidate launch shape (threads per block
-along x, rows per block along y) with HIP events on the simulation's stream
-and persists the fastest in tiles.json next to this file, keyed by "NXxNY".
+For a lattice size it times every candidate launch shape of the strips (threads
+per block along x, rows per block along y; they take the steps that patches do
+not: a call's last, checking steps, thin lattices) with HIP events on the
+simulation's stream and persists the fastest in tiles.json next to this file, keyed by "NXxNY".
 `tune_pad` does the same for the padding between the workspace's planes
 (lbf_params.plane_pad) of the plane-major layout (and of the 3D lattice),
 which decides how the 34 planes that one step streams spread over the HBM
@@ -50,14 +51,20 @@ def lookup(nx: int, ny: int) -> Optional[Tuple[int, int]]:
 
 def tune(sim, steps: int = 20, candidates: Iterable[Sequence[int]] = CANDIDATES,
          save: bool = True) -> Tuple[Tuple[int, int], dict]:
-    """Time each candidate on `sim` (its state advances) and keep the best."""
+    """Time each candidate on `sim` (its state advances) and keep the best.
+
+    A call's steps but the last are taken on patches, whatever the launch
+    shape, so each step timed is a call of its own."""
     times = {}
     sim.set_timing(True)
     for tx, ty in candidates:
         sim.set_tile(tx, ty)
         sim.step(2)
-        sim.step(steps)
-        times[f"{tx}x{ty}"] = sim.last_step_kernel_ms()
+        total = 0.0
+        for _ in range(steps):
+            sim.step(1)
+            total += sim.last_step_kernel_ms()
+        times[f"{tx}x{ty}"] = total / steps
     sim.set_timing(False)
     best = min(times, key=times.get)
     tile = tuple(int(v) for v in best.split("x"))
@@ -200,14 +207,20 @@ def lookup_batch(count: int, nodes: int) -> Optional[Tuple[int, int]]:
 
 def tune_batch(batch, steps: int = 64, candidates: Iterable[Sequence[int]] = BATCH_CANDIDATES,
                save: bool = True) -> Tuple[Tuple[int, int], dict]:
-    """Time each tile shape on a batch (its lattices advance) and keep the best."""
+    """Time each tile shape on a batch (its lattices advance) and keep the best.
+
+    Pairs of steps are taken on patches, whatever the tile, so each step timed
+    is a call of its own."""
     times = {}
     batch.set_timing(True)
     for tx, ty in candidates:
         batch.set_tile(tx, ty)
-        batch.step(steps)          # first call builds the work list and the graph
-        batch.step(steps)
-        times[f"{tx}x{ty}"] = batch.last_step_ms()
+        batch.step(1)              # the first call builds the work list
+        total = 0.0
+        for _ in range(steps):
+            batch.step(1)
+            total += batch.last_step_ms()
+        times[f"{tx}x{ty}"] = total / steps
     batch.set_timing(False)
     best = min(times, key=times.get)
     tile = tuple(int(v) for v in best.split("x"))

@@ -373,7 +373,7 @@ class Sim:
 
 
 class Batch:
-    """Many lattices advanced together by one persistent launch per step."""
+    """Many lattices advanced together by one launch per pair of steps."""
 
     def __init__(self, sims: Sequence[Sim], tile: Optional[Sequence[int]] = None):
         L = load()
