@@ -618,12 +618,39 @@ int check_stable(lbf_sim* s, const double* part, long long level) {
 
 }  // namespace
 
+// Pairs in the runs of steps that no stability check (every k levels) interrupts, of
+// `n` steps from level `step` on.
+static long long pairs_between_checks(long long step, long long n, int k) {
+  if (k <= 0) return n / 2;
+  const long long first = (k - step % k) % k;
+  if (n <= first) return n / 2;
+  const long long rest = n - first;
+  return first / 2 + rest / k * ((k - 1) / 2) + (rest % k ? (rest % k - 1) / 2 : 0);
+}
+
+// Whether the caller is capturing the stream's work into a graph.
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return c == hipStreamCaptureStatusActive;
+}
+
 int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
   if (nsteps == 0) return LBF_OK;
   if (s->timing) HIP_TRY(hipEventRecord(s->ev0, s->stream));
   const int k = s->prm.check_every;
   const bool patches = takes_patches(s), single = patches_of(s, kPatchSteps) <= kPatches1;
   const int most = patches_of(s, 3) <= kPatches3 ? 3 : kPatchSteps;
+  const int end = budget ? nsteps - 1 : nsteps;
+  // Every launch turns the two states over.  A captured call takes an even number of
+  // pairs: the state is then in the buffer that step by step it would be in, and a
+  // call of an even number of steps replays from where it ended.
+  long long pairs = most == 2 ? pairs_between_checks(s->step, end, k) : 0;
+  const bool captured = capturing(s->stream);
+  if (captured) pairs = pairs / 2 * 2;
   for (int it = 0; it < nsteps; ++it) {
     const bool last = budget && it == nsteps - 1;
     // a checking step reduces the state it reads (time level s->step)
@@ -631,9 +658,10 @@ int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
     if (patches && !last && !chk) {
       // up to the next step that reduces its state
       int K = 1;
-      const int end = budget ? nsteps - 1 : nsteps;
       while (K < most && it + K < end && !(k > 0 && (s->step + K) % k == 0)) ++K;
+      if (most == 3 ? K == 2 && captured : K == 2 && pairs == 0) K = 1;
       if (K > 1 || single) {
+        if (most == 2 && K == 2) --pairs;
         int rc = launch_patches(s, make_args(s), K, s->stream);
         if (rc) return rc;
         s->cur = 1 - s->cur;
@@ -1351,9 +1379,12 @@ int lbf_batch_step(lbf_batch* b, int32_t nsteps) {
       done += kGraphSteps;
     }
   }
+  // an even number of pairs in a captured call here too (see advance)
+  int pairs = most == kPatchSteps ? (nsteps - done) / 2 : 0;
+  if (capturing(b->stream)) pairs = pairs / 2 * 2;
   int parity = 0;
   while (done < nsteps) {
-    const int n = std::min(most, nsteps - done);
+    const int n = pairs-- > 0 ? kPatchSteps : 1;
     int rc = batch_launch(b, n, parity, b->stream);
     if (rc) return rc;
     parity ^= 1;

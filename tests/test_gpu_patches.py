@@ -6,6 +6,7 @@ smaller than one, with every kind of side, and around checking steps."""
 import copy
 import functools
 
+import numpy as np
 import pytest
 
 from paper_2510_18688_amd import workloads as W
@@ -104,3 +105,27 @@ def test_batch_of_patches(lbf_mod, mrt, thin):
             x.save_state(sx)
             y.save_state(sy)
             assert torch.equal(sx, sy), (steps, x.nx, x.ny, x.case.mat.mrt)
+
+
+@pytest.mark.parametrize("name", ["most_three_steps", "too_many_for_three", "seven"])
+@pytest.mark.parametrize("steps", [2, 4, 6, 8, 10])
+def test_captured_call_replays(lbf_mod, name, steps):
+    """A captured call of an even number of steps ends in the buffer it began in,
+    however its steps were grouped: replays continue from one another."""
+    import torch
+    stream = torch.cuda.Stream()
+    a = lbf_mod.Sim(CASES[name](), check_every=0, stream=stream)
+    b = lbf_mod.Sim(CASES[name](), check_every=0)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        a.step(steps)
+    # (the fields, not the saved states: a replay does not turn the host's step count)
+    for _ in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        stream.synchronize()
+        b.step(steps)
+        fa, fb = a.fields(), b.fields()
+        for k in fa:
+            assert (fa[k].view(np.uint32) == fb[k].view(np.uint32)).all(), k
