@@ -130,8 +130,7 @@ int recompute_steps(lbf_tape* t, const float* in, float* out, float* mom, int K,
   B.dout = out;
   B.lout = out + NDIST * t->P;
   B.fields = mom;
-  // (strips against patches, us a step: 1024^2 99, 73; 256^2 at the default tile 89, 9)
-  if (takes_patches(s)) return launch_patches(s, B, K, st, kStatePlanes * t->P, 3 * t->P);
+  if (records_on_patches(s)) return launch_patches(s, B, K, st, kStatePlanes * t->P, 3 * t->P);
   return launch_step_args(s, MODE_STEP_MOM, false, B, st);
 }
 
@@ -143,7 +142,7 @@ int recompute_segment(lbf_tape* t, int sgi, bool buffer_used) {
   const int c = sgi * t->seg;
   const int L = std::min(t->seg, t->nsteps - c);
   if (buffer_used) HIP_TRY(hipStreamWaitEvent(t->rstream, t->ev_used[b], 0));
-  const int most = takes_patches(t->sim) ? kPatchSteps : 1;
+  const int most = records_on_patches(t->sim) ? kPatchSteps : 1;
   for (int j = 0; j < L;) {
     const int K = std::min(most, L - j);
     const float* in = j == 0 ? state_ptr(t, 0, sgi) : state_ptr(t, 1 + b, j - 1);

@@ -514,6 +514,15 @@ bool lbfi::takes_patches(const lbf_sim* s) {
   return s->G.nx >= kPatchLeast && s->G.ny >= kPatchLeast;
 }
 
+// A recorded step writes 39 planes, and a patch's rows of 24 nodes are not whole lines:
+// where a strip's are, and there are more than 8000 patches, strips record (a reversed
+// step with its recomputation, strips against patches, us: 256^2 27, 26; 1024^2 at the
+// tile of the nearest size measured 234, 221; 2048 x 1024 415, 436; 2048^2 814, 864;
+// 1000 x 700 164, 154; 1400 x 1000 342, 317).
+bool lbfi::records_on_patches(const lbf_sim* s) {
+  return takes_patches(s) && (s->G.nx % 32 != 0 || patches_of(s, kPatchSteps) <= kPatches1);
+}
+
 int lbfi::launch_patches(const lbf_sim* s, BufArgs B, int K, hipStream_t st, size_t state_stride,
                          size_t mom_stride) {
   int nbx = 0;

@@ -119,6 +119,8 @@ int launch_step_args(lbf_sim* s, int mode, bool red, lbf::BufArgs B, hipStream_t
 int advance(lbf_sim* s, int nsteps, bool budget);
 // Whether the lattice's steps are taken in pairs on patches.
 bool takes_patches(const lbf_sim* s);
+// Whether a segment of a recorded run is recomputed on patches.
+bool records_on_patches(const lbf_sim* s);
 // One to three steps on patches from B's state into its other one; with a stride also
 // the state of every step and the moments of each, `state_stride` and
 // `mom_stride` floats apart (BGK only).
