@@ -263,8 +263,11 @@ enum {
 };
 int lbf_profiles(lbf_sim* sim, double* col, double* row, int32_t dst_on_device);
 
-/* Launch shape of the step kernel: threads per block along x (64, 128, 256,
- * 512) and rows per block along y (>= 1).  Defaults are chosen at creation. */
+/* Launch shape of the step kernel's strips: threads per block along x (64, 128,
+ * 256, 512) and rows per block along y (>= 1).  Defaults are chosen at creation.
+ * Strips take a call's last step, the steps that a stability check reduces, and
+ * lattices fewer than 8 nodes thin; the others run on patches of one shape, two or
+ * three steps a launch. */
 int lbf_set_tile(lbf_sim* sim, int32_t tile_x, int32_t tile_y);
 int lbf_get_tile(const lbf_sim* sim, int32_t* tile_x, int32_t* tile_y);
 
@@ -277,8 +280,8 @@ size_t lbf_state_bytes(const lbf_sim* sim);
 int lbf_save_state(lbf_sim* sim, void* dst_device, size_t cap);
 int lbf_load_state(lbf_sim* sim, const void* src_device, size_t bytes);
 
-/* Average duration in milliseconds of the step kernel over the launches of
- * the last lbf_step call, from HIP events on the simulation's stream (0 if
+/* Average duration in milliseconds of a step over the launches of the last
+ * lbf_step call, from HIP events on the simulation's stream (0 if
  * timing is off).  lbf_set_timing(sim, 1) brackets each launch with events. */
 int lbf_set_timing(lbf_sim* sim, int32_t on);
 double lbf_last_step_kernel_ms(const lbf_sim* sim);

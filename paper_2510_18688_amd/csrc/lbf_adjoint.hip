@@ -3,8 +3,8 @@
 //
 // The forward run stores the state every `segment` steps (sqrt(N) by
 // default).  The backward sweep walks the segments from last to first:
-// recompute the segment from its checkpoint with the step kernel (which also
-// stores phi, f_s and rho of every state for the reverse stencils), then
+// recompute the segment from its checkpoint on patches or strips (which also
+// store phi, f_s and rho of every state for the reverse stencils), then
 // run the two adjoint kernels per step in reverse order.  The recomputation
 // of segment k - 1 does not depend on the adjoint, so it runs on a second
 // stream into the other of two segment buffers while segment k is reversed;
