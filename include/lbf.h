@@ -212,7 +212,11 @@ int lbf_init_fields(lbf_sim* sim, const float* phi, const float* T, int32_t on_d
 int lbf_set_poststream_state(lbf_sim* sim, const float* dist, const float* lag, int64_t step,
                              int32_t on_device);
 
-/* Advance nsteps coupled time steps (nsteps >= 0).  Asynchronous on the
+/* Advance nsteps coupled time steps (nsteps >= 0).  A call of an even number
+ * of steps ends in the buffer it began in, so that a HIP graph captured from
+ * one may be replayed before and after other calls of even numbers of steps,
+ * and after lbf_init_fields if it was captured with an even number of steps
+ * taken since the last one.  Asynchronous on the
  * simulation's stream, except for the stability checks that
  * lbf_params.check_every asks for: LBF_EUNSTABLE (message naming the time
  * level) when one fails; the steps up to and including the checking step

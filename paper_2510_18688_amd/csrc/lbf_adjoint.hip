@@ -237,11 +237,17 @@ int lbf_tape_forward(lbf_tape* t) {
     return fail(LBF_EINVAL, "the adjoint supports the phi0 >= 1/2 held region only, not a "
                             "per-node isothermal region");
   t->with_init = s->from_fields && s->step == 0;
+  // the budget is the run's last step's
+  auto steps_from = [&](int c) { return std::min(t->seg, t->nsteps - c); };
+  auto reduces = [&](int c) { return c + steps_from(c) == t->nsteps; };
+  long long pairs = 0;
+  for (int c = 0; c < t->nsteps; c += t->seg)
+    pairs += pairs_of(s, s->step + c, steps_from(c), reduces(c));
+  Turns turns(s, pairs);
   for (int c = 0; c < t->nsteps; c += t->seg) {
     int rc = copy_state_out(t, state_ptr(t, 0, c / t->seg));
     if (rc) return rc;
-    const int n = std::min(t->seg, t->nsteps - c);
-    rc = advance(s, n, c + n == t->nsteps);   // the budget is the run's last step's
+    rc = advance(s, steps_from(c), reduces(c), turns);
     if (rc) return rc;
   }
   t->recorded = true;

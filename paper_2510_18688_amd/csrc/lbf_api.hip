@@ -647,19 +647,35 @@ static bool capturing(hipStream_t st) {
   return c == hipStreamCaptureStatusActive;
 }
 
-int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
+// Steps of one launch on patches: two, or three on the smallest lattices.
+static int steps_a_launch(const lbf_sim* s) {
+  return patches_of(s, 3) <= kPatches3 ? 3 : kPatchSteps;
+}
+
+long long lbfi::pairs_of(const lbf_sim* s, long long step, int nsteps, bool budget) {
+  if (!takes_patches(s) || steps_a_launch(s) != 2) return 0;
+  return pairs_between_checks(step, budget ? nsteps - 1 : nsteps, s->prm.check_every);
+}
+
+// Where a call that a stability check ends has turned the states over an odd number of
+// times more than its steps would: the state goes to the other buffer.
+static int settle(lbf_sim* s, const Turns& t) {
+  if (((s->cur ^ t.cur) & 1) == ((s->step - t.step) & 1)) return LBF_OK;
+  const size_t bytes =
+      (size_t)array_floats(s->G.nblk, s->G.GS, s->G.P, kStateSlots) * sizeof(float);
+  HIP_TRY(hipMemcpyAsync(s->ws + s->L.dist[1 - s->cur], s->ws + s->L.dist[s->cur], bytes,
+                         hipMemcpyDeviceToDevice, s->stream));
+  s->cur = 1 - s->cur;
+  return LBF_OK;
+}
+
+int lbfi::advance(lbf_sim* s, int nsteps, bool budget, Turns& t) {
   if (nsteps == 0) return LBF_OK;
   if (s->timing) HIP_TRY(hipEventRecord(s->ev0, s->stream));
   const int k = s->prm.check_every;
   const bool patches = takes_patches(s), single = patches_of(s, kPatchSteps) <= kPatches1;
-  const int most = patches_of(s, 3) <= kPatches3 ? 3 : kPatchSteps;
+  const int most = steps_a_launch(s);
   const int end = budget ? nsteps - 1 : nsteps;
-  // Every launch turns the two states over.  A captured call takes an even number of
-  // pairs: the state is then in the buffer that step by step it would be in, and a
-  // call of an even number of steps replays from where it ended.
-  long long pairs = most == 2 ? pairs_between_checks(s->step, end, k) : 0;
-  const bool captured = capturing(s->stream);
-  if (captured) pairs = pairs / 2 * 2;
   for (int it = 0; it < nsteps; ++it) {
     const bool last = budget && it == nsteps - 1;
     // a checking step reduces the state it reads (time level s->step)
@@ -668,9 +684,9 @@ int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
       // up to the next step that reduces its state
       int K = 1;
       while (K < most && it + K < end && !(k > 0 && (s->step + K) % k == 0)) ++K;
-      if (most == 3 ? K == 2 && captured : K == 2 && pairs == 0) K = 1;
+      if (K == 2 && t.pairs == 0) K = 1;
       if (K > 1 || single) {
-        if (most == 2 && K == 2) --pairs;
+        if (K == 2) --t.pairs;
         int rc = launch_patches(s, make_args(s), K, s->stream);
         if (rc) return rc;
         s->cur = 1 - s->cur;
@@ -690,7 +706,8 @@ int lbfi::advance(lbf_sim* s, int nsteps, bool budget) {
         dim3 grid;
         s->budget_blocks = grid_blocks(s, grid);
         s->have_budget = last;
-        return rc;
+        const int moved = settle(s, t);
+        return moved ? moved : rc;
       }
     }
   }
@@ -918,7 +935,8 @@ int lbf_step(lbf_sim* s, int32_t nsteps) {
   if (!s) return fail(LBF_EINVAL, "sim is NULL");
   if (nsteps < 0) return fail(LBF_EINVAL, "nsteps %d", nsteps);
   if (!s->have_init) return fail(LBF_ESTATE, "lbf_init_fields must precede lbf_step");
-  return advance(s, nsteps, true);
+  Turns t(s, pairs_of(s, s->step, nsteps, true));
+  return advance(s, nsteps, true, t);
 }
 
 int lbf_read_fields(lbf_sim* s, float* dst, int32_t dst_on_device) {
@@ -1388,7 +1406,7 @@ int lbf_batch_step(lbf_batch* b, int32_t nsteps) {
       done += kGraphSteps;
     }
   }
-  // an even number of pairs in a captured call here too (see advance)
+  // an even number of pairs in a captured call here too (see Turns)
   int pairs = most == kPatchSteps ? (nsteps - done) / 2 : 0;
   if (capturing(b->stream)) pairs = pairs / 2 * 2;
   int parity = 0;

@@ -114,9 +114,23 @@ int launch_read_out(lbf_sim* s, uint32_t mask, float* dst, int stride);
 // Launch the step kernel (MODE_STEP, MODE_FIELDS or MODE_STEP_MOM) with the
 // simulation's tile shape on explicit buffers, on stream `st`.
 int launch_step_args(lbf_sim* s, int mode, bool red, lbf::BufArgs B, hipStream_t st);
-// lbf_step; without `budget` the last step is like the others and leaves no step
+// Turns of a call.  Every launch turns the two states over, whether it takes one, two
+// or three steps, and a captured graph holds the buffers of its capture: so each call,
+// captured or not, leaves the state in the buffer that step by step it would be in.  It
+// takes an even number of pairs, counted over the whole call; the steps of an odd one are
+// launches of their own (20 steps of 4096 x 2048, nine pairs 9.12 ms, eight 9.39).
+struct Turns {
+  long long pairs;   // still to be taken
+  int cur;           // buffer and time level that the call began with
+  long long step;
+  Turns(const lbf_sim* s, long long free_pairs)
+      : pairs(free_pairs / 2 * 2), cur(s->cur), step(s->step) {}
+};
+// Pairs that `nsteps` steps from level `step` on hold (see advance).
+long long pairs_of(const lbf_sim* s, long long step, int nsteps, bool budget);
+// Steps of a call; without `budget` the last step is like the others and leaves no step
 // budget for lbf_reduce.
-int advance(lbf_sim* s, int nsteps, bool budget);
+int advance(lbf_sim* s, int nsteps, bool budget, Turns& t);
 // Whether the lattice's steps are taken in pairs on patches.
 bool takes_patches(const lbf_sim* s);
 // Whether a segment of a recorded run is recomputed on patches.

@@ -129,3 +129,99 @@ def test_captured_call_replays(lbf_mod, name, steps):
         fa, fb = a.fields(), b.fields()
         for k in fa:
             assert (fa[k].view(np.uint32) == fb[k].view(np.uint32)).all(), k
+
+
+def _same_fields(a, b, when):
+    fa, fb = a.fields(), b.fields()
+    for k in fa:
+        assert (fa[k].view(np.uint32) == fb[k].view(np.uint32)).all(), (when, k)
+
+
+@pytest.mark.parametrize("name", ["most_three_steps", "too_many_for_three", "seven"])
+@pytest.mark.parametrize("steps", [2, 4, 6, 8])
+@pytest.mark.parametrize("check", [0, 9])
+def test_replays_among_eager_calls(lbf_mod, name, steps, check):
+    """Any call of an even number of steps ends in the buffer it began in, captured or
+    not: a replay finds the fields set after the capture and what eager calls leave."""
+    import torch
+    case = CASES[name]()
+    stream = torch.cuda.Stream()
+    a = lbf_mod.Sim(case, check_every=check, stream=stream)
+    b = lbf_mod.Sim(case, check_every=0)
+    a.step(10)                       # levels 10 .. 17 hold no check
+    a.step(0 if check else steps)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        a.step(steps)
+
+    def replay():
+        with torch.cuda.stream(stream):
+            graph.replay()
+        stream.synchronize()
+        b.step(steps)
+
+    a.init_fields(case.phi, case.T)
+    replay()
+    _same_fields(a, b, "set after the capture")
+    for n in (steps, 4, 12):
+        a.step(n)
+        b.step(n)
+        _same_fields(a, b, ("eager", n))
+        replay()
+        _same_fields(a, b, ("replay after", n))
+
+
+def test_replay_after_an_unstable_call(lbf_mod):
+    """A call that a stability check ends leaves the state in the buffer that step by
+    step it would, so that a replay continues from a state loaded after it."""
+    import torch
+    case = CASES["too_many_for_three"]()
+    stream = torch.cuda.Stream()
+    a = lbf_mod.Sim(case, check_every=4, stream=stream)
+    b = lbf_mod.Sim(case, check_every=0)
+    a.step(5)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        a.step(2)
+    a.init_fields(case.phi, case.T)
+    a.step(5)
+    b.step(5)
+    saved = torch.empty(a.state_bytes(), dtype=torch.uint8, device="cuda")
+    a.save_state(saved)
+    a.set_wall_temperature(0, np.full(a.nx, np.nan))
+    with pytest.raises(lbf_mod.LbfError):
+        a.step(9)                    # levels 5, 6, 7, then the check at 8
+    a.set_wall_temperature(0, case.wall_profile(0))
+    a.load_state(saved)
+    with torch.cuda.stream(stream):
+        graph.replay()
+    stream.synchronize()
+    b.step(2)
+    # the replay turned the buffers twice: the state is where the host has it
+    _same_fields(a, b, "replay")
+
+
+@pytest.mark.parametrize("n, seg", [(4, 4), (6, 2), (8, 3), (10, 10)])
+def test_recorded_run_keeps_the_turn(lbf_mod, n, seg):
+    """A recorded run of an even number of steps ends in the buffer it began in,
+    whatever its segments (replays after it)."""
+    import torch
+    case = CASES["too_many_for_three"]()
+    case.mat.phi_src_mdot = 1
+    stream = torch.cuda.Stream()
+    a = lbf_mod.Sim(case, check_every=0, stream=stream, row_block=0)
+    b = lbf_mod.Sim(case, check_every=0, row_block=0)
+    tape = lbf_mod.Tape(a, n, seg)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        a.step(2)
+    a.init_fields(case.phi, case.T)
+    tape.forward()
+    with torch.cuda.stream(stream):
+        graph.replay()
+    stream.synchronize()
+    b.step(n + 2)
+    _same_fields(a, b, (n, seg))
