@@ -310,7 +310,9 @@ void lbf_destroy(lbf_sim* sim);
 /* ---- batches: many lattices advanced by one launch per pair of steps ----
  * A batch groups n initialised simulations that share one HIP stream (the
  * simulations stay owned by the caller and must outlive the batch).  Two
- * steps are one launch over the patches of every lattice; a step left over, and
+ * steps are one launch over the patches of every lattice; a step left over (of
+ * each run of four steps, so that a call of an even number of steps ends in the
+ * buffers it began in, see lbf_step), and
  * every step of a batch with a lattice fewer than 8 nodes thin, is one launch
  * of a fixed grid (as many workgroups as fit on the device at once) that walks
  * the work list of every lattice's tiles.  Runs of 32 steps are captured once

@@ -637,16 +637,6 @@ static long long pairs_between_checks(long long step, long long n, int k) {
   return first / 2 + rest / k * ((k - 1) / 2) + (rest % k ? (rest % k - 1) / 2 : 0);
 }
 
-// Whether the caller is capturing the stream's work into a graph.
-static bool capturing(hipStream_t st) {
-  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return c == hipStreamCaptureStatusActive;
-}
-
 // Steps of one launch on patches: two, or three on the smallest lattices.
 static int steps_a_launch(const lbf_sim* s) {
   return patches_of(s, 3) <= kPatches3 ? 3 : kPatchSteps;
@@ -1406,9 +1396,11 @@ int lbf_batch_step(lbf_batch* b, int32_t nsteps) {
       done += kGraphSteps;
     }
   }
-  // an even number of pairs in a captured call here too (see Turns)
-  int pairs = most == kPatchSteps ? (nsteps - done) / 2 : 0;
-  if (capturing(b->stream)) pairs = pairs / 2 * 2;
+  // An even number of pairs here too (see Turns), so that a call of an even number of
+  // steps needs no new descriptors after it, nor a synchronisation to upload them: the
+  // steps of an odd pair go to strips (five lattices of 64^2 .. 500 x 300, two steps: 45
+  // us as a pair, 79 so; six: 97, 130).
+  int pairs = most == kPatchSteps ? (nsteps - done) / 4 * 2 : 0;
   int parity = 0;
   while (done < nsteps) {
     const int n = pairs-- > 0 ? kPatchSteps : 1;

@@ -225,3 +225,40 @@ def test_recorded_run_keeps_the_turn(lbf_mod, n, seg):
     stream.synchronize()
     b.step(n + 2)
     _same_fields(a, b, (n, seg))
+
+
+def _batch_pair(lbf_mod, stream):
+    names = ["walls", "eight", "one_over", "one_under"]
+    return ([lbf_mod.Sim(CASES[n](), check_every=0, stream=stream) for n in names],
+            [lbf_mod.Sim(CASES[n](), check_every=0) for n in names])
+
+
+@pytest.mark.parametrize("steps", [2, 4, 6])
+def test_batch_replays_among_eager_calls(lbf_mod, steps):
+    """A batched call of an even number of steps ends in the buffers it began in: graphs
+    captured before it still replay from the state, and neither the capture nor a call
+    after it needs new descriptors."""
+    import torch
+    stream = torch.cuda.Stream()
+    a, b = _batch_pair(lbf_mod, stream)
+    batch = lbf_mod.Batch(a)
+    batch.step(2)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        batch.step(steps)
+
+    def both(n, f):
+        f()
+        stream.synchronize()
+        for x, y in zip(a, b):
+            y.step(n)
+            _same_fields(x, y, n)
+
+    for y in b:
+        y.step(2)
+    with torch.cuda.stream(stream):
+        for n in (2, 6, 34):
+            both(steps, graph.replay)
+            both(n, lambda: batch.step(n))
+        both(steps, graph.replay)
