@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void k_ch_step2(ChGeo G, const float* __restri
   const int t = lbf::xcd_tile(blockIdx.x, gridDim.x) * 4 + wave_of_block();
   if (t >= nstrips) return;
   const int nx = G.n[0], ny = G.n[1];
-  const int xs = (t % nsx) * W, ys = (t / nsx) * rows, ye = min(ys + rows, ny);
+  const int xs = (t % nsx) * W, ys = (t / nsx) * rows, ye = ys + min(rows, ny - ys);
   const int lane = threadIdx.x & 63;
   int gx[V], ox[V];
 #pragma unroll
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
   const int wv = wave_of_block(), lane = threadIdx.x & 63;
   const int xs = (t % nsx) * W, yb = ((t / nsx) % nsy) * H, zs = (t / (nsx * nsy)) * slabs;
   const int ys = yb - 1 + wv * R;   // the lane's first row
-  const int ze = min(zs + slabs, nz);
+  const int ze = zs + min(slabs, nz - zs);
   const int gx = source_node(xs + lane - 2, nx, G.per[0]);
   const bool mine = lane >= 2 && lane < 62 && xs + lane - 2 < nx;
   const int below = max(wv - 1, 0), above = min(wv + 1, 3);
@@ -336,7 +336,10 @@ __global__ __launch_bounds__(256) void k_ch_final(const float* __restrict__ c,
 
 size_t plane_bytes(long long n) { return ((size_t)n * 4 + 255) / 256 * 256; }
 
-int ceil_div(int a, int b) { return (a + b - 1) / b; }
+int ceil_div(int a, int b) { return (int)(((long long)a + b - 1) / b); }
+
+// Longest sides the passes take: the coordinates of a strip and its overlap stay ints.
+constexpr int kMaxSide[3] = {0x7FFFFFFF - 63, 0x7FFFFFFF - 15, 0x7FFFFFFF - 3};
 
 // Checks shared by both entry points.
 int ch_validate(const lbf_ch_params* p, int32_t iterations) {
@@ -395,6 +398,9 @@ int ch_pass3(const ChGeo& G, const float* c, const uint8_t* img, float* cn, floa
 // Stream-ordered; synchronises only when host memory is read or written.
 int ch_run(const lbf_ch_params* p, const uint8_t* solid, bool solid_on_device, float* phi0,
            bool phi0_on_device, int32_t iterations, hipStream_t st, float* c0, float* c1) {
+  if (iterations > 0 && (p->nx > kMaxSide[0] || p->ny > kMaxSide[1] || p->nz > kMaxSide[2]))
+    return fail(LBF_EINVAL, "image of %d x %d x %d nodes: sides up to %d, %d, %d", p->nx, p->ny,
+                p->nz, kMaxSide[0], kMaxSide[1], kMaxSide[2]);
   const int N = p->nx * p->ny * p->nz;
   float* c[2] = {c0, c1};
   const int nb = (int)(((long long)N + 255) / 256);

@@ -302,3 +302,16 @@ def test_ch_noalloc_refuses_on_host(L):
     assert L.lbf_ch_smooth_noalloc(C.byref(p), None, out, 1, None) == -1
     assert L.lbf_ch_smooth_noalloc(None, buf, out, 1, None) == -1
     assert list(out) == [3.0, 3.0, 3.0, 3.0]
+
+
+@pytest.mark.parametrize("shape, axis", [((1, 2 ** 31 - 1), "x"), ((2 ** 31 - 1, 1), "y"), ((2 ** 31 - 1, 1, 1), "z")])
+def test_ch_longest_sides_refused_on_host(L, shape, axis):
+    """Sides that no pass takes (the coordinates of a strip with its overlap would not
+    fit an int) are refused before any device call."""
+    from paper_2510_18688_amd import porous
+    porous._declare(L)
+    p = porous.ch_params(shape, (False,) * len(shape))
+    need = L.lbf_ch_workspace_bytes(p.nx, p.ny, p.nz)
+    dummy = C.c_void_p(4096)      # never read or written
+    assert L.lbf_ch_smooth(C.byref(p), dummy, 1, dummy, 1, 1, None, dummy, need) == -1, axis
+    assert "sides up to" in L.lbf_last_error().decode()

@@ -64,3 +64,36 @@ def test_result_inside_the_workspace(P, shape, iters):
                                   iters, st, C.c_void_p(ws.data_ptr()), need))
         got = ws[off:off + 4 * img.numel()].view(torch.float32).reshape(shape)
         assert torch.equal(got, want), off
+
+
+@pytest.mark.parametrize("tail, iters", [((1,), 4), ((1, 1), 1)])
+def test_longest_columns(P, tail, iters):
+    """One column of close to 2^31 nodes: strips of the last rows and slabs end where the
+    image does.  The image repeats every 4099 nodes, so the result does, away from the
+    walls; near them it is that of the image's first and last nodes alone."""
+    import torch
+    from paper_2510_18688_amd import lbf
+    L = lbf.load()
+    P._declare(L)
+    p, n = 4099, 2 ** 31 - 20000
+    need = L.lbf_ch_workspace_bytes(n, 1, 1)
+    if torch.cuda.mem_get_info()[0] < 1.3 * (need + 7 * n):
+        pytest.skip("needs 41 GB of device memory")
+    g = torch.Generator().manual_seed(3)
+    tile = (torch.rand(p, generator=g) < 0.5).to(torch.uint8).cuda()
+    img = tile.repeat(n // p + 1)[:n]
+
+    def smooth(a):
+        out = torch.empty(a.numel(), dtype=torch.float32, device="cuda")
+        q = P.ch_params((a.numel(),) + tail, (False,) * (1 + len(tail)))
+        size = L.lbf_ch_workspace_bytes(q.nx, q.ny, q.nz)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        lbf.check(L.lbf_ch_smooth(C.byref(q), C.c_void_p(a.data_ptr()), 1, C.c_void_p(out.data_ptr()), 1, iters,
+                                  C.c_void_p(torch.cuda.current_stream().cuda_stream), C.c_void_p(ws.data_ptr()), size))
+        return out
+
+    got = smooth(img)
+    first, last = smooth(img[:3 * p].clone()), smooth(img[-3 * p:].clone())
+    m = n // p
+    assert bool((got[p:(m - 1) * p].view(m - 2, p) == first[p:2 * p]).all())
+    assert torch.equal(got[:p], first[:p]) and torch.equal(got[-2 * p:], last[-2 * p:])
