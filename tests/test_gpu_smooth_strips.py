@@ -97,3 +97,16 @@ def test_longest_columns(P, tail, iters):
     m = n // p
     assert bool((got[p:(m - 1) * p].view(m - 2, p) == first[p:2 * p]).all())
     assert torch.equal(got[:p], first[:p]) and torch.equal(got[-2 * p:], last[-2 * p:])
+
+
+@pytest.mark.parametrize("wrap", [False, True])
+@pytest.mark.parametrize("ny", [1, 2, 3, 4, 6, 7, 10, 11, 13, 14, 15, 17])
+def test_columns_of_few_rows(P, ny, wrap):
+    """3D images whose last strip leaves some of a workgroup's wavefronts (four rows each,
+    the first from -1) without rows."""
+    from oracle import ch_oracle
+    shape = (9, ny, 7)
+    img = (np.random.default_rng(ny).random(shape) < 0.5).astype(np.uint8)
+    per = (wrap, wrap, not wrap)
+    err = float(np.abs(P.ch_smooth(img, per, 3).astype(np.float64) - ch_oracle.smooth(img, per, 3)).max())
+    assert err <= TOL, (ny, wrap, err)
