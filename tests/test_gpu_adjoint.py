@@ -234,3 +234,39 @@ def test_gradient_workload_256_against_fp64_reference(lbf_mod):
         print("  direction", r, flush=True)
     assert cos >= COSINE, cos
     assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("nx, ny, h_s, radius", [(7, 24, 3.0, 8.0), (32, 7, 2.0, 4.0)])
+def test_thin_lattices(lbf_mod, nx, ny, h_s, radius):
+    """Fewer than eight nodes thin: segments are recomputed on strips."""
+    case = W.small_freezing_case(nx, ny, h_s=h_s, radius=radius)
+    rng = np.random.default_rng(20)
+    target = 0.3 * rng.uniform(0, 1, (ny, nx))
+    run_case(lbf_mod, case, 30, misfit_loss(target, a_T=0.01 * rng.normal(size=(ny, nx))), seed=5)
+
+
+def test_large_lattice_of_whole_lines(lbf_mod):
+    """More than 8000 patches and rows of whole lines: segments are recomputed on strips.
+    The lattice repeats a narrow one, recomputed on patches, 32 times along x: so do its
+    fields and gradients, bit for bit (each node's and wall entry's sum is its own)."""
+    import torch
+    times, nx, ny, steps = 32, 64, 752, 4
+    small = W.slab_drop(nx, ny, 20.0, 75.0 + 10.0 * np.random.default_rng(21).uniform(-1, 1, nx), -1.5, h_s=3.0)
+    small.mat.phi_src_mdot = 1
+    big = W.slab_drop(times * nx, ny, 20.0, 75.0, -1.5, h_s=3.0, mat=small.mat)
+    for k in ("phi0", "cos_theta", "phi", "T"):
+        setattr(big, k, np.tile(getattr(small, k), (1, times)))
+    seeds = np.random.default_rng(22).normal(size=(3, ny, nx)).astype(np.float32)
+    got = []
+    for case, n in ((small, 1), (big, times)):
+        sim = lbf_mod.Sim(case, row_block=0)
+        tape = lbf_mod.Tape(sim, steps, 3)
+        tape.forward()
+        gc, gw = tape.backward(*[torch.as_tensor(np.tile(s, (1, n)), device="cuda") for s in seeds])
+        fs = sim.field("fs", torch.empty((ny, n * nx), dtype=torch.float32, device="cuda"))
+        got.append([fs, gc, gw[:n * nx].view(1, -1), gw[n * nx:2 * n * nx].view(1, -1)])
+        assert float(gc.abs().max()) > 0 and float(gw[:n * nx].abs().max()) > 0
+        tape.close()
+        sim.close()
+    for a, b in zip(*got):
+        assert torch.equal(a.repeat(1, times), b)

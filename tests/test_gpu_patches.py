@@ -262,3 +262,31 @@ def test_batch_replays_among_eager_calls(lbf_mod, steps):
             both(steps, graph.replay)
             both(n, lambda: batch.step(n))
         both(steps, graph.replay)
+
+
+@pytest.mark.parametrize("nx, ny", [(2048, 800), (1999, 801)])
+def test_large_lattices(lbf_mod, nx, ny):
+    """More than 8000 patches: pairs on patches, the steps between them on strips."""
+    import torch
+    a = lbf_mod.Sim(_slab(nx, ny, True, False), check_every=4)
+    b = lbf_mod.Sim(_slab(nx, ny, True, False), check_every=0)
+    sa = torch.empty(a.state_bytes(), dtype=torch.uint8, device="cuda")
+    sb = torch.empty_like(sa)
+    for steps in (7, 10):
+        a.step(steps)
+        for _ in range(steps):
+            b.step(1)
+        a.save_state(sa)
+        b.save_state(sb)
+        assert torch.equal(sa, sb), steps
+
+
+@pytest.mark.parametrize("tile", [(64, 1), (64, 7), (128, 32), (256, 5), (256, 200), (512, 3), (512, 16)])
+def test_tiles_step_by_step(lbf_mod, tile):
+    """Every step a call's last, so that all of them march strips of the tile."""
+    case = _slab(150, 70, True, False)
+    a, b = lbf_mod.Sim(case, tile=tile), lbf_mod.Sim(case, tile=(64, 32))
+    b.step(20)
+    for _ in range(20):
+        a.step(1)
+    _same_fields(a, b, tile)
