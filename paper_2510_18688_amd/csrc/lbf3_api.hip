@@ -584,7 +584,6 @@ int lbf3_create(const lbf3_params* params, void* stream, void* workspace, size_t
   }
   s->G.rmask = rb ? rb - 1 : 0x7fffffff;
   s->G.nblk = s->L.nblk;
-  s->G.RBN = rb * params->nx;
   s->G.AS = (int)s->L.AS;
   s->G.PL = (int)s->L.PL;
   s->stream = (hipStream_t)stream;

@@ -68,7 +68,6 @@ struct Geo3 {
   int rbs, rmask;    // log2 and rb - 1 of the rows per block (31, 0x7fffffff: one block)
   int gss;           // log2 of the block stride GS (31: one block)
   int nblk;          // blocks
-  int RBN;           // nodes per block (rb nx)
   int AS;            // floats from one state array to the next (f, g, h)
   int PL;            // plane stride of the linear arrays (records, read-out)
   float Tw[6];       // face temperatures
@@ -481,26 +480,6 @@ __device__ __forceinline__ void collide3_h(const Phys& ph, const Mom& m, const C
 #pragma unroll
   for (int i = 1; i < NQ; ++i) hv[i] = hn[i];
   lbf::two_sum(ref_h, hn[0], hhi, hv[0]);
-}
-
-// The whole collision of one node, in place on fv, gv, hv (gv[0], hv[0] as
-// deviations from the node's references).
-__device__ __forceinline__ void collide3(const Phys& ph, const Mom& m, const Stencil3& S,
-                                         float phi0, float cth, float lap_phi0,
-                                         const float* jprev, float ref_h, float* fv, float* gv,
-                                         float* hv, Post3& o) {
-  Coll3 c;
-  collide3_prepare(ph, m, S, phi0, cth, lap_phi0, jprev, fv, c);
-  collide3_f(c, fv);
-  collide3_g(ph, m, c, gv, o.ghi);
-  collide3_h(ph, m, c, phi0, ref_h, hv, o.hhi);
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    o.u[a] = c.u[a];
-    o.j[a] = c.j[a];
-  }
-  o.p = c.p;
-  o.Q = c.Q;
 }
 
 }  // namespace lbf3
