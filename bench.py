@@ -34,12 +34,16 @@ BYTES_PER_LU = (27 + 5) * 2 * 4 + 3 * 4
 # the previous step is then the product of phi and u, so the lagged fields
 # are f_s, Q, phi, p, u_x, u_y.
 METHOD_BYTES_PER_LU = (27 + 6) * 2 * 4 + 3 * 4
-# What this implementation's step kernel moves by design: those 27
-# distributions and 6 lagged fields plus one plane holding the 16-bit high
-# parts of the float-float rest populations g_0, h_0 (7 lagged planes) read
-# and written, and 2 static planes read (phi0, cos theta; lap phi0 is formed
-# from phi0 in the kernel).
-IMPL_BYTES_PER_LU = (27 + 7) * 2 * 4 + 2 * 4
+# What the implementation moves by design, per step: pairs of steps on patches
+# (patch_kernel) read and write those 27 distributions and 6 lagged fields plus
+# one plane holding the 16-bit high parts of the float-float rest populations
+# g_0, h_0 (7 lagged planes; 6 with the mass source, whose (phi u) stands for
+# phi and u) once for both steps, and read 3 static planes (phi0, cos theta, lap
+# phi0).  A call's last step, and one that a stability check reduces, march
+# strips: the same planes for one step, without lap phi0 (280 B).
+STEPS_PER_LAUNCH = 2
+IMPL_BYTES_PER_LU = ((27 + 7) * 2 * 4 + 3 * 4) / STEPS_PER_LAUNCH
+IMPL_BYTES_PER_LU_MDOT = ((27 + 6) * 2 * 4 + 3 * 4) / STEPS_PER_LAUNCH
 HBM_PEAK_GBS = 8000.0
 # D3Q19, two kernels per step, with the phase-field source from the flow's
 # divergence.  Moments pass: g and h pulled (38 planes), the high parts of
@@ -57,7 +61,7 @@ BYTES3_STATE = (57 + 11) * 2 * 4 + 3 * 4
 BYTES_CH = 4 + 4
 
 
-def hbm_traffic(kernel_ms, name="step_kernel_curved_substrate_2048x2048"):
+def hbm_traffic(name):
     """HBM traffic of a kernel from a committed rocprofv3 counter summary
     (FETCH_SIZE and WRITE_SIZE per dispatch, scaled by the same counters'
     reading of a plain 512 MiB copy); None when the kernel sources changed
@@ -284,7 +288,7 @@ def d3q19(lbf, torch, steps):
             "state_bytes_frac": round(BYTES3_STATE * n / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
             "nonfinite": red["nonfinite"], "umax": red["umax"],
         }
-        rec = hbm_traffic(ms, "d3q19_kernels_" + label) if n == 16777216 else None
+        rec = hbm_traffic("d3q19_kernels_" + label) if n == 16777216 else None
         if rec is not None:
             per_lu = sum((k["hbm_bytes_per_launch"] / n) for k in rec["kernels"].values())
             out[label]["traffic_bytes_per_lu"] = round(per_lu, 1)
@@ -320,7 +324,7 @@ def mrt(lbf, W, torch, steps, tile, pad, rb):
 def mass_source(lbf, W, torch, steps, tile, pad, rb):
     """The headline workload with the model's mass source as the phase-field
     source's divergence (phi_src_mdot = 1) instead of the previous step's
-    velocity divergence: no velocity planes, the lagged (phi u) stored, 272
+    velocity divergence: no velocity planes, the lagged (phi u) stored, 138
     bytes per update moved by the kernel; stable over shorter runs only."""
     case = W.curved_substrate()
     case.mat.phi_src_mdot = 1
@@ -340,8 +344,9 @@ def mass_source(lbf, W, torch, steps, tile, pad, rb):
     return {"workload": case.name + " with the mass source as div u (phi_src_mdot 1)",
             "steps": steps, "mlups": round(case.nodes * steps / wall / 1e6, 1),
             "kernel_ms": round(kms, 5), "achieved_gbs": round(gbs, 1),
-            "frac": round(gbs / HBM_PEAK_GBS, 4), "impl_bytes_per_lu": 272,
-            "impl_frac": round(272 * case.nodes / (kms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+            "frac": round(gbs / HBM_PEAK_GBS, 4), "impl_bytes_per_lu": IMPL_BYTES_PER_LU_MDOT,
+            "impl_frac": round(IMPL_BYTES_PER_LU_MDOT * case.nodes / (kms * 1e-3) / 1e9
+                               / HBM_PEAK_GBS, 4),
             "nonfinite": red["nonfinite"]}
 
 
@@ -474,13 +479,14 @@ def main():
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
 
-    # kernel duration from HIP events on the simulation's stream
+    # duration of a step in the kernels, from HIP events on the simulation's stream
     sim.set_timing(True)
     sim.step(args.steps)
     kms = sim.last_step_kernel_ms()
     sim.set_timing(False)
     red = sim.reduce()
-    # the same access pattern with no arithmetic: the ceiling the step can reach
+    # the strips' access pattern with no arithmetic: what a step would take that moves
+    # its state once by itself (pairs of steps on patches move it once for two)
     copy_ms, copy_bytes = sim.copy_probe(max(args.steps, 20))
 
     # observables: column and row profiles of the final state
@@ -495,12 +501,13 @@ def main():
     nodes = case.nodes
     mlups = nodes * args.steps / wall / 1e6
     achieved = BYTES_PER_LU * nodes / (kms * 1e-3) / 1e9
-    counters = hbm_traffic(kms)
+    counters = hbm_traffic("patch_kernel_curved_substrate_2048x2048")
     traffic = None
     traffic_per_lu = None
-    if counters is not None:
-        traffic = round(counters["hbm_bytes_per_launch"] / (kms * 1e-3) / 1e9, 1)
-        traffic_per_lu = round(counters["hbm_bytes_per_launch"] / nodes, 1)
+    if counters is not None:   # per step: a launch takes two
+        traffic_per_lu = counters["hbm_bytes_per_launch"] / nodes / counters["steps_per_launch"]
+        traffic = round(traffic_per_lu * nodes / (kms * 1e-3) / 1e9, 1)
+        traffic_per_lu = round(traffic_per_lu, 1)
     out = {
         "metric": "MLUPS of coupled 3-field LB step, % of HBM peak; adjoint/forward time ratio",
         "value": round(mlups, 2),
@@ -518,9 +525,12 @@ def main():
                    "tile": f"{tile[0]}x{tile[1]}", "plane_pad": pad, "row_block": rb,
                    "steps_per_run": case.steps},
         "pct_hbm": round(100.0 * mlups * 1e6 * BYTES_PER_LU / (HBM_PEAK_GBS * 1e9), 2),
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+        # the vector units bound the kernel (profiles/patch_kernels.txt); the rate is priced
+        # in bytes, one trip of the state a step, as the metric is
+        "roofline": {"bound": "valu", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "kernel": "patch_kernel",
+                     "steps_per_launch": STEPS_PER_LAUNCH,
                      "kernel_ms": round(kms, 5), "bytes_per_lu": BYTES_PER_LU,
                      "impl_bytes_per_lu": IMPL_BYTES_PER_LU,
                      "impl_frac": round(IMPL_BYTES_PER_LU * nodes / (kms * 1e-3) / 1e9
@@ -531,8 +541,8 @@ def main():
                      "traffic_bytes_per_launch": counters and counters["hbm_bytes_per_launch"],
                      "traffic_bytes_per_lu": traffic_per_lu,
                      "traffic_over_algorithmic": counters and round(
-                         counters["hbm_bytes_per_launch"] / (BYTES_PER_LU * nodes), 4)},
-        "copy_ceiling": {"kernel": "k_copy_probe (the step's planes, tiles and row order; "
+                         traffic_per_lu / BYTES_PER_LU, 4)},
+        "copy_ceiling": {"kernel": "k_copy_probe (a strip step's planes, tiles and row order; "
                                    "no arithmetic)",
                          "ms": round(copy_ms, 5),
                          "bytes_per_lu": round(copy_bytes / nodes, 1),

@@ -269,9 +269,11 @@ int lbf_profiles(lbf_sim* sim, double* col, double* row, int32_t dst_on_device);
 
 /* Launch shape of the step kernel's strips: threads per block along x (64, 128,
  * 256, 512) and rows per block along y (>= 1).  Defaults are chosen at creation.
- * Strips take a call's last step, the steps that a stability check reduces, and
- * lattices fewer than 8 nodes thin; the others run on patches of one shape, two or
- * three steps a launch. */
+ * Strips take a call's last step, the steps that a stability check reduces, steps
+ * between pairs on lattices of more than 8000 patches (about 1.5 million nodes), the
+ * recomputation of recorded runs on such lattices when their rows are whole lines
+ * (nx a multiple of 32), read-outs and reductions, and lattices fewer than 8 nodes
+ * thin; the other steps run on patches of one shape, two or three a launch. */
 int lbf_set_tile(lbf_sim* sim, int32_t tile_x, int32_t tile_y);
 int lbf_get_tile(const lbf_sim* sim, int32_t* tile_x, int32_t* tile_y);
 
@@ -286,7 +288,8 @@ int lbf_load_state(lbf_sim* sim, const void* src_device, size_t bytes);
 
 /* Average duration in milliseconds of a step over the launches of the last
  * lbf_step call, from HIP events on the simulation's stream (0 if
- * timing is off).  lbf_set_timing(sim, 1) brackets each launch with events. */
+ * timing is off).  lbf_set_timing(sim, 1) records one event before the call's
+ * launches and one after them. */
 int lbf_set_timing(lbf_sim* sim, int32_t on);
 double lbf_last_step_kernel_ms(const lbf_sim* sim);
 

@@ -12,10 +12,12 @@
 // another), so K steps deliver the inner (TX - 4 K) x (TY - 4 K) nodes; the rings are
 // computed by the neighbouring patches as well.
 //
-// What bounds it is the vector instructions (78 % busy at 1400 x 1000), of the nodes
-// computed twice too: at 32 x 16 and two steps 1.67 collisions and 2.33 pulls per node
-// and step delivered, rows of wholly outer nodes skipped.  2048^2: 201 us a step
-// against 233 of strips and 187 of the state's traffic once at 6.2 TB/s (halved here).
+// What bounds it is the vector instructions (76 % busy at 2048^2, 1410 per node and step;
+// under MRT 83 %, 1860), of the nodes computed twice too: at 32 x 16 and two steps 1.67
+// collisions and 2.33 pulls per node and step delivered, rows of wholly outer nodes
+// skipped.  A pair moves 299 + 136 bytes a node (the rings are half found in L2; 148 +
+// 136 without them), 4.5 TB/s.  2048^2: 201 us a step against 233 of strips, which move
+// 301 bytes in each.
 // Patches of 32 x 32 and 64 x 16 compute less twice, but one fills a compute unit and
 // nothing runs beside its barriers and loads (1400 x 1000: 99 and 95 us against 75).
 //

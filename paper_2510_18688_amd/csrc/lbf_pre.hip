@@ -41,7 +41,12 @@ constexpr long long kMaxNodesCH = 0x7FFFFFFFLL;
 // within 2 %.  256^3: 4 rows a lane, 2280 / 3040 / 4180 / 6080 wavefronts 58.5 / 41.7
 // / 46.1 / 40.5; 6 rows 51.6 / 45.5 / 45.8 / 44.3; 8 rows 55.2 / 52.5 / 45.1 / 47.1; every
 // wavefront with its own overlap along y (no LDS) 45 at best.  One step a pass
-// through a tile of c and of mu in LDS took 25.2 (2D) and 98 (3D).
+// through a tile of c and of mu in LDS took 25.2 (2D) and 98 (3D).  Other sizes, 2048 /
+// 3072 / 4096 / 5500 wavefronts: 1024^2 3.5 / 3.8 / 3.8 / 3.8, 2000^2 7.1 / 6.7 / 7.3 /
+// 7.9, 3333 x 1111 6.6 / 6.7 / 6.6 / 6.9; 3D, 3072 / 4096 / 6144 / 8192: 160^3 16.4 / 16.6 /
+// 18.2 / 18.2, 250 x 170 x 90 19.0 / 16.7 / 18.1 / 18.1, 200^3 29.0 / 24.4 / 25.6 / 26.7.  The
+// same lines serve all of them within a tenth.  At least four slabs a strip (1 / 2 / 4:
+// 20^3 6.0 / 6.7 / 8.1, 64^3 8.0 / 7.7 / 8.2, 128^3 16.0 / 16.2 / 14.1).
 constexpr int kT2 = 4, kV2 = 1, kPF2 = 4, kWaves2 = 4096;
 constexpr int kR3 = 4, kWaves3 = 6144;
 
