@@ -48,8 +48,9 @@ size_t lbf_ch_workspace_bytes(int32_t nx, int32_t ny, int32_t nz);
  * `workspace`: caller-owned device memory of lbf_ch_workspace_bytes(), 256-byte
  * aligned, or NULL for a library allocation freed before return.  Ordered on
  * `stream` (NULL: the default stream); returns after the result is written
- * when either side is host memory.  LBF_EINVAL for bad sizes or coefficients
- * and for a step outside the explicit scheme's linear stability bound
+ * when either side is host memory.  LBF_EINVAL for bad sizes or coefficients,
+ * for steps of an image with nx, ny or nz above 2^31 - 64, - 16 or - 4, and for
+ * a step outside the explicit scheme's linear stability bound
  * dt M (16/3) (2 A + kappa 16/3) <= 2 (16/3 is the largest magnitude of the
  * lattice Laplacian's eigenvalues on both lattices). */
 int lbf_ch_smooth(const lbf_ch_params* params, const uint8_t* solid, int32_t solid_on_device,
